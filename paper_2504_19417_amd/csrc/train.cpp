@@ -2,6 +2,7 @@
 // argument checks and the launch of one training step.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <new>
 
@@ -18,11 +19,11 @@ struct veckm_trainer {
 namespace {
 
 constexpr int kHeadBlocks = 512;
-constexpr int kMaxSplits = 64;
+constexpr int kMaxSplits = 256;  // row splits of dW1, times its tiles per split
 
 void free_state(TrainState& s) {
-  float* bufs[] = {s.theta, s.grad, s.m1, s.m2, s.H, s.dZ, s.head_part, s.w1_part};
-  for (float* b : bufs)
+  void* bufs[] = {s.theta, s.m1, s.m2, s.dZ, s.head_part, s.w1_part, s.frag, s.bad};
+  for (void* b : bufs)
     if (b) (void)hipFree(b);
   s = TrainState{};
 }
@@ -51,13 +52,17 @@ int veckm_trainer_create(int32_t d, int32_t hidden, int64_t max_rows, const floa
   s.head_blocks = kHeadBlocks;
   s.max_splits = kMaxSplits;
   const int64_t np = (int64_t)hidden * s.k2 + 3 * (int64_t)hidden + 2;
-  auto alloc = [](float** p, int64_t count) {
-    return dev_malloc(reinterpret_cast<void**>(p), (size_t)count * sizeof(float));
+  const int64_t row_tiles = (max_rows + 31) / 32;
+  // (a step splits the rows over at most kMaxSplits blocks in all, at least two row tiles each)
+  const int64_t splits = std::min<int64_t>(kMaxSplits, (row_tiles + 1) / 2);
+  auto alloc = [](auto** p, int64_t count) {
+    return dev_malloc(reinterpret_cast<void**>(p), (size_t)count * sizeof(**p));
   };
-  bool ok = alloc(&s.theta, np) && alloc(&s.grad, np + 1) && alloc(&s.m1, np) &&
-            alloc(&s.m2, np) && alloc(&s.H, max_rows * hidden) && alloc(&s.dZ, max_rows * hidden) &&
+  bool ok = alloc(&s.theta, np) && alloc(&s.m1, np) && alloc(&s.m2, np) &&
+            alloc(&s.dZ, (max_rows + kTrainBlockRows - 1) / kTrainBlockRows * kTrainBlockRows * hidden) &&
             alloc(&s.head_part, (int64_t)kHeadBlocks * (3 * hidden + 3)) &&
-            alloc(&s.w1_part, (int64_t)kMaxSplits * hidden * s.k2);
+            alloc(&s.w1_part, splits * hidden * s.k2) &&
+            alloc(&s.frag, (int64_t)hidden * ((s.k2 + 15) / 16 * 16) * 3) && alloc(&s.bad, 1);
   if (ok) {
     float* p = s.theta;
     ok = hipMemcpy(p, W1, (size_t)hidden * s.k2 * 4, hipMemcpyHostToDevice) == hipSuccess &&
@@ -69,6 +74,8 @@ int veckm_trainer_create(int32_t d, int32_t hidden, int64_t max_rows, const floa
              hipSuccess &&
          hipMemset(s.m1, 0, (size_t)np * 4) == hipSuccess &&
          hipMemset(s.m2, 0, (size_t)np * 4) == hipSuccess &&
+         hipMemset(s.bad, 0, sizeof(int)) == hipSuccess &&
+         launch_train_init(s, nullptr) == VECKM_OK &&
          hipDeviceSynchronize() == hipSuccess;
   }
   if (!ok) {
@@ -100,15 +107,9 @@ int veckm_trainer_step(veckm_trainer* tr, const float* emb, const float* target,
     c1 = (float)(1.0 / (1.0 - std::pow(0.9, (double)t)));
     c2 = (float)(1.0 / (1.0 - std::pow(0.999, (double)t)));
   }
-  const int rc = launch_train_step(tr->s, emb, target, m, optimizer, lr, c1, c2, stream);
+  const int rc = launch_train_step(tr->s, emb, target, m, optimizer, lr, c1, c2, loss, stream);
   if (rc) return rc;
   if (optimizer == 1) ++tr->t;
-  if (loss) {
-    const int64_t np = (int64_t)tr->s.hidden * tr->s.k2 + 3 * (int64_t)tr->s.hidden + 2;
-    if (hipMemcpyAsync(loss, tr->s.grad + np, sizeof(float), hipMemcpyDeviceToDevice,
-                       (hipStream_t)stream) != hipSuccess)
-      return VECKM_E_HIP;
-  }
   return VECKM_OK;
 }
 

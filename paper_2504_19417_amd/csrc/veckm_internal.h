@@ -291,28 +291,31 @@ int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event
                           const EncodeTables& et, void* stream);
 
 // ------------------------------------------------------------ perceptron training
-// Device state of a trainer: parameters and gradients in the order W1
-// [hidden][k2], b1, W2 [2][hidden], b2 (the gradient buffer has one more
-// slot: the step's loss), Adam moments, layer-1 activations and their
-// gradients for max_rows rows, and partial-sum buffers.
+constexpr int kTrainBlockRows = 256;  // most rows a block of the forward kernel takes
+// Device state of a trainer: parameters in the order W1 [hidden][k2], b1, W2
+// [2][hidden], b2, Adam moments, the gradients of the layer-1 pre-activations
+// for max_rows rows (in the order of the matrix-core accumulators), W1 as
+// three bf16 terms in fragment order, and partial-sum buffers.
 struct TrainState {
   int k2 = 0, hidden = 0;
   int64_t max_rows = 0;
   float* theta = nullptr;
-  float* grad = nullptr;
   float* m1 = nullptr;
   float* m2 = nullptr;
-  float* H = nullptr;
-  float* dZ = nullptr;
+  float* dZ = nullptr;         // max_rows rounded up to kTrainBlockRows, x hidden
   float* head_part = nullptr;  // head_blocks x (3 hidden + 3)
-  float* w1_part = nullptr;    // max_splits x hidden x k2
+  float* w1_part = nullptr;    // row splits x hidden x k2
+  uint16_t* frag = nullptr;    // k2 rounded up to 16, x hidden x 3
+  int* bad = nullptr;          // set once W1 holds a value beyond the bf16 terms' range
   int head_blocks = 0, max_splits = 0;
 };
+// Fills frag from theta.
+int launch_train_init(const TrainState& s, void* stream);
 // One step on m rows x [m][k2] (device) with targets y [m][2] (device):
 // forward, loss, gradients, update (adam 0: gradient descent; 1: Adam with
-// bias corrections c1, c2).  Leaves the loss in grad[n_params].
+// bias corrections c1, c2).  Writes the step's loss to `loss` if not NULL.
 int launch_train_step(const TrainState& s, const float* x, const float* y, int64_t m, int adam,
-                      float lr, float c1, float c2, void* stream);
+                      float lr, float c1, float c2, float* loss, void* stream);
 
 // ------------------------------------------------- context hooks for the server
 // What one call can hold, and what one slice needs of it.
