@@ -382,8 +382,9 @@ int run(veckm_ctx* c, const Workspace& w, const Batch& bt, const veckm_event* ev
   const int64_t nlines = (int64_t)bt.nbricks * c->et.brick.by * c->et.brick.bt;
   {
     StageTimer t(c, VECKM_STAGE_PREPARE, stream);
-    const int rc = c->window ? launch_window_prepare(bt, w, ev, c->et, stream)
-                             : launch_prepare(bt, w, ev, queries, c->et, !c->paper, stream);
+    const int rc = c->window ? launch_window_prepare(bt, w, ev, c->et, c->num_cus, stream)
+                             : launch_prepare(bt, w, ev, queries, c->et, !c->paper, c->num_cus,
+                                             stream);
     if (rc) {
       if (clear) (void)launch_clear_grids(bt, w, nlines, stream);
       return rc;
@@ -640,8 +641,8 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
     if (hipMemcpy(druns[i], runs.data(), runs.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
       rc = VECKM_E_HIP;
   }
-  if (!rc && druns1) {  // a single voxel's count box (rows of bricks with few rows)
-    const std::vector<int32_t> runs = make_run_offsets(st, Brick{1, 1, 1}, params->rx, params->ry);
+  if (!rc && druns1) {  // single rows (of bricks with few rows)
+    const std::vector<int32_t> runs = make_run_triples(st);
     if (hipMemcpy(druns1, runs.data(), runs.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
       rc = VECKM_E_HIP;
   }
@@ -676,12 +677,9 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
     t.nbuf = tl[i].nbuf;
     t.layout = tl[i].layout;
     t.runs = druns[i];
-    // single rows: as many single-voxel boxes as fit in the brick's box (up
-    // to one 16-row tile); worth it from 8 on
     t.runs1 = druns1;
-    const int vol1 = box_dwords(Brick{1, 1, 1}, params->rx, params->ry, rt_enc);
-    t.rs = std::min(16, box_dwords(t.brick, params->rx, params->ry, rt_enc) / vol1);
-    t.sp = druns1 && t.rs >= 8 ? kSparseBelow : 0;
+    t.rs = encode_single_rows(t);
+    t.sp = druns1 && t.rs >= 16 ? kSparseBelow : 0;
     c->tilings.push_back(t);
   }
   c->et = c->tilings[0];
@@ -1037,7 +1035,7 @@ int veckm_tune(veckm_ctx* ctx, const veckm_slice* slices, int32_t count,
       if (!rc) rc = multi_batch(ctx, slices, count, events, events, stream, &bt, &slot);
       if (!rc && bt.m > 0) {
         // (the grids return to zero as in a batch call)
-        rc = launch_prepare(bt, ctx->w, events, nullptr, ctx->et, true, stream);
+        rc = launch_prepare(bt, ctx->w, events, nullptr, ctx->et, true, ctx->num_cus, stream);
         if (!rc)
           rc = launch_encode(bt, ctx->w, ctx->et, rows, ctx->num_cus, stream, nullptr,
                              &ctx->mw);

@@ -1,0 +1,8 @@
+// Instances of the encoder kernel (FP16 form, D = 256).
+#include "encode_kernel.h"
+
+namespace veckm {
+
+template int launch_layout<2, 16>(const EncArgs&, const EncodeTables&, int, int, hipStream_t);
+
+}  // namespace veckm

@@ -16,6 +16,8 @@
 // window, event range and region of the shared grids, and the bricks of all
 // slices form one work list.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <hip/hip_fp16.h>
 
 #include "slices.h"
@@ -186,7 +188,7 @@ template <bool ALL, int kIt>
 __global__ __launch_bounds__(256) void k_rank(Batch bt, Brick b, const int32_t* __restrict__ count,
                                               uint8_t* __restrict__ qmark,
                                               int32_t* __restrict__ rank,
-                                              int32_t* __restrict__ ulist,
+                                              uint16_t* __restrict__ ulist,
                                               int32_t* __restrict__ brick_nq) {
   __shared__ int wave_tot[4];
   const int gb = blockIdx.x;
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(256) void k_rank(Batch bt, Brick b, const int32_t* 
         const int64_t v = voxel(li);
         rank[v] = r;
         if (!ALL) qmark[v] = 0;  // the marks are clear again for the next call
-        ulist[(int64_t)gb * BV + r] = li;
+        ulist[(int64_t)gb * BV + r] = (uint16_t)li;
       }
       base += __popcll(bal[k]);
     }
@@ -267,15 +269,30 @@ __global__ __launch_bounds__(256) void k_rank(Batch bt, Brick b, const int32_t* 
 // A flagged row lies inside the slice (flags come from valid events only);
 // its voxels beyond the slice's x edge are skipped.  Dynamic LDS: 4 waves x
 // by x bt row numbers (uint16).
+//
+// Both kernels write the bits of every brick x row (flagged or not): the
+// encoder collects a single row's window from them.
+//
+// The words of a step's x rows (bx consecutive lanes each, a lane's voxel has
+// `count` events), one store per row.
+__device__ inline void put_bits(int count, bool valid, uint2* at, int lane, int bx) {
+  const unsigned long long bo = __ballot(count == 1 || count > 2), bm = __ballot(count > 1);
+  if (valid && (lane & (bx - 1)) == 0) {
+    const uint32_t mask = bx >= 32 ? ~0u : (1u << bx) - 1u;
+    *at = make_uint2((uint32_t)(bo >> lane) & mask, (uint32_t)(bm >> lane) & mask);
+  }
+}
+
 template <bool ALL>
 __global__ __launch_bounds__(256) void k_rank_lines(Batch bt, Brick b,
                                                     const int32_t* __restrict__ count,
                                                     uint8_t* __restrict__ lines,
                                                     uint8_t* __restrict__ qmark,
                                                     int32_t* __restrict__ rank,
-                                                    int32_t* __restrict__ ulist,
+                                                    uint16_t* __restrict__ ulist,
                                                     int32_t* __restrict__ brick_nq,
                                                     uint32_t* __restrict__ pairs,
+                                                    uint2* __restrict__ bits,
                                                     int32_t* __restrict__ err) {
   constexpr int kG = 8, kU = 8;
   extern __shared__ uint16_t rl_rows[];
@@ -303,6 +320,8 @@ __global__ __launch_bounds__(256) void k_rank_lines(Batch bt, Brick b,
         if (f[u]) {
           rows[nr + __popcll(bal & below)] = (uint16_t)l;
           fl[l] = 0;
+        } else if (l < NL) {
+          bits[(int64_t)gb * NL + l] = make_uint2(0u, 0u);
         }
         nr += __popcll(bal);
       }
@@ -372,13 +391,15 @@ __global__ __launch_bounds__(256) void k_rank_lines(Batch bt, Brick b,
         }
         f = ALL ? hi > 0 : qmark[s.grid_off + at(li)] != 0;
       }
+      put_bits(cv[g], (k0 + g) * rps + slot < nr,
+               bits + (int64_t)gb * NL + (li >> sx), lane, b.bx);
       const unsigned long long bal = __ballot(f);
       if (f) {
         const int64_t v = s.grid_off + at(li);
         const int r = base + __popcll(bal & below);
         rank[v] = r;
         if (!ALL) qmark[v] = 0;  // the marks are clear again for the next call
-        ulist[(int64_t)gb * BV + r] = li;
+        ulist[(int64_t)gb * BV + r] = (uint16_t)li;
       }
       base += __popcll(bal);
     }
@@ -398,9 +419,10 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
                                                      uint8_t* __restrict__ lines,
                                                      uint8_t* __restrict__ qmark,
                                                      int32_t* __restrict__ rank,
-                                                     int32_t* __restrict__ ulist,
+                                                     uint16_t* __restrict__ ulist,
                                                      int32_t* __restrict__ brick_nq,
                                                      uint32_t* __restrict__ pairs,
+                                                     uint2* __restrict__ bits,
                                                      int32_t* __restrict__ err) {
   constexpr int kG = 8;
   constexpr int kSteps = kMaxBrickVoxels / 64;
@@ -420,6 +442,7 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
     }
   }
   if (!__syncthreads_or(any)) {
+    for (int l = threadIdx.x; l < NL; l += NW * 64) bits[(int64_t)gb * NL + l] = make_uint2(0u, 0u);
     if (threadIdx.x == 0) brick_nq[gb] = 0;
     return;
   }
@@ -455,8 +478,12 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
     }
     if (!__ballot(anyf)) {
 #pragma unroll
-      for (int g = 0; g < kG; ++g)
+      for (int g = 0; g < kG; ++g) {
+        const int li = (k0 + g) * 64 + lane;
         if (k0 + g < k_hi && lane == 0) sbal[k0 + g] = 0ull;
+        put_bits(0, k0 + g < k_hi && li < BV, bits + (int64_t)gb * NL + (li >> sx), lane,
+                 b.bx);
+      }
       continue;
     }
     int cv[kG], side[kG];
@@ -486,6 +513,8 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
         }
         f = ALL ? hi > 0 : qmark[s.grid_off + at(li)] != 0;
       }
+      put_bits(cv[g], k0 + g < k_hi && li < BV,
+               bits + (int64_t)gb * NL + (li >> sx), lane, b.bx);
       const unsigned long long bal = __ballot(f);
       if (k0 + g < k_hi && lane == 0) sbal[k0 + g] = bal;
       tot += __popcll(bal);
@@ -510,7 +539,7 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
       const int r = base + __popcll(bal & below);
       rank[v] = r;
       if (!ALL) qmark[v] = 0;  // the marks are clear again for the next call
-      ulist[(int64_t)gb * BV + r] = li;
+      ulist[(int64_t)gb * BV + r] = (uint16_t)li;
     }
     base += __popcll(bal);
   }
@@ -571,13 +600,20 @@ static_assert(kScanNV == kScanClasses + 2 && kScanTile % kScanThreads == 0, "sca
 
 // Bricks with fewer than `sp` rows (0: none) are not the encoder's work
 // items: their rows are numbered after all other rows and listed one by one
-// in srow ({brick, brick-local voxel} per row), and the encoder takes them
-// in items of up to `rs` rows, each row with a count box of its own.
+// in srow ({slice, slice-local voxel} per row, k_list_rows), and the encoder
+// takes them in items of up to `rs` rows.
 struct SparseRows {
-  int sp = 0, rs = 1, bv = 0;
-  const int32_t* ulist = nullptr;
-  int2* srow = nullptr;
+  int sp = 0, rs = 16, cus = 1;
 };
+
+// Single rows per item: full items once there is work for every CU several
+// times over (`bricks` whole ones among it), fewer rows (whole 16-row tiles)
+// below that, so that a small call spreads over the CUs.
+__device__ inline int single_rows_per_item(int us, int bricks, const SparseRows& sr) {
+  if (bricks + us / sr.rs >= 2 * sr.cus) return sr.rs;
+  const int even = ((us + sr.cus - 1) / sr.cus + 15) & ~15;
+  return even < 16 ? 16 : even < sr.rs ? even : sr.rs;
+}
 
 __device__ inline bool sparse_brick(int q, int sp) { return q > 0 && q < sp; }
 
@@ -669,10 +705,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_totals(const int32_t* __r
 // One block: turns the tile totals into each tile's starting positions
 // (class k of tile b starts at the class's start plus the class counts of
 // tiles before b; rows likewise).
-__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(int ntiles, int nb, int rs,
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(int ntiles, int nb,
+                                                             SparseRows sr,
                                                              int32_t* __restrict__ part,
                                                              int32_t* __restrict__ off,
-                                                             int4* __restrict__ order,
                                                              int32_t* __restrict__ plan) {
   __shared__ int sums[kScanNV][kScanThreads];
   const int tid = threadIdx.x;
@@ -715,16 +751,16 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(int ntiles, int nb,
       part[i * kScanNV + k] = run[k];
       run[k] += t;
     }
-  // the single-row items follow the bricks in the work list
-  const int ns = (us + rs - 1) / rs;
-  for (int j = tid; j < ns; j += kScanThreads)
-    order[acc + j] = make_int4(kSparseTag | j, min(rs, us - j * rs), ud + j * rs, j * rs);
   if (tid == 0) {
+    const int per_item = single_rows_per_item(us, acc, sr);
     off[nb] = ud + us;
     plan[0] = ud + us;
     plan[1] = 0;
-    plan[2] = acc + ns;
+    plan[2] = acc + (us + per_item - 1) / per_item;
     plan[3] = ud;
+    plan[4] = acc;
+    plan[5] = per_item;
+    plan[6] = start[kScanClasses - 1];
   }
 }
 
@@ -742,7 +778,6 @@ __global__ __launch_bounds__(NT) void k_scan_place(Batch bt,
   static_assert(ONE || NT == kScanThreads, "tiles of kScanTile bricks");
   scan_tile<NT>(nq, nb, ch, SP ? sr.sp : 0, blockIdx.x, q, v, ex, tot);
   int pos[kScanNV];
-  int ud;  // rows of the bricks taken whole: single rows start here
   if constexpr (ONE) {
     int start = 0;
 #pragma unroll
@@ -750,26 +785,23 @@ __global__ __launch_bounds__(NT) void k_scan_place(Batch bt,
       pos[k] = start + ex[k];
       start += tot[k];
     }
-    ud = tot[kRowsD];
+    const int ud = tot[kRowsD];  // rows of the bricks taken whole: single rows start here
     pos[kRowsD] = ex[kRowsD];
     pos[kRowsS] = ud + ex[kRowsS];
-    // the single-row items follow the bricks in the work list
-    const int us = SP ? tot[kRowsS] : 0, ns = SP ? (us + sr.rs - 1) / sr.rs : 0;
-    if constexpr (SP)
-      for (int j = threadIdx.x; j < ns; j += NT)
-        order[start + j] = make_int4(kSparseTag | j, min(sr.rs, us - j * sr.rs), ud + j * sr.rs,
-                                     j * sr.rs);
     if (threadIdx.x == 0) {
+      const int us = SP ? tot[kRowsS] : 0, per_item = single_rows_per_item(us, start, sr);
       off[nb] = ud + us;
       plan[0] = ud + us;
       plan[1] = 0;
-      plan[2] = start + ns;
+      plan[2] = start + (us + per_item - 1) / per_item;
       plan[3] = ud;
+      plan[4] = start;
+      plan[5] = per_item;
+      plan[6] = start - tot[kScanClasses - 1];
     }
   } else {
 #pragma unroll
     for (int k = 0; k < kScanNV; ++k) pos[k] = part[blockIdx.x * kScanNV + k] + ex[k];
-    ud = plan[3];
   }
   const int i0 = blockIdx.x * (NT * kScanPer) + threadIdx.x * kScanPer;
 #pragma unroll
@@ -777,15 +809,7 @@ __global__ __launch_bounds__(NT) void k_scan_place(Batch bt,
     const int i = i0 + u;
     if (i >= nb) break;
     if (SP && sparse_brick(q[u], sr.sp)) {
-      // its rows, one by one, among the single rows (all loads at once)
       off[i] = pos[kRowsS];
-      int li[kSparseBelow - 1];
-#pragma unroll
-      for (int r = 0; r < kSparseBelow - 1; ++r)
-        li[r] = r < q[u] ? sr.ulist[(int64_t)i * sr.bv + r] : 0;
-#pragma unroll
-      for (int r = 0; r < kSparseBelow - 1; ++r)
-        if (r < q[u]) sr.srow[pos[kRowsS] - ud + r] = make_int2(i, li[r]);
       pos[kRowsS] += q[u];
       continue;
     }
@@ -807,6 +831,40 @@ __global__ __launch_bounds__(NT) void k_scan_place(Batch bt,
       }
       order[p] = make_int4(i, q[u], pos[kRowsD] - q[u], sl);
     }
+  }
+}
+
+// Lists the single rows: a wave per brick; those of fewer than sp rows write
+// {slice, voxel} of each row.
+__global__ __launch_bounds__(256) void k_list_rows(Batch bt, Brick b, int sp,
+                                                   const int32_t* __restrict__ brick_nq,
+                                                   const int32_t* __restrict__ brick_off,
+                                                   const uint16_t* __restrict__ ulist,
+                                                   const int32_t* __restrict__ plan,
+                                                   int2* __restrict__ srow) {
+  const int gb = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (gb >= bt.nbricks) return;
+  const int q = brick_nq[gb];
+  if (!sparse_brick(q, sp)) return;
+  const int first = brick_off[gb] - plan[3];
+  int si = 0;
+  if (bt.nslices > 1) {
+    int hi = bt.nslices - 1;
+    while (si < hi) {
+      const int mid = (si + hi + 1) >> 1;
+      if (bt.table[mid].brick_off <= gb) si = mid; else hi = mid - 1;
+    }
+  }
+  const SliceDesc s = bt.nslices == 1 ? bt.s0 : bt.table[si];
+  const int lb = gb - s.brick_off;
+  const int bxi = lb % s.nbx, byi = (lb / s.nbx) % s.nby, bti = lb / (s.nbx * s.nby);
+  const int sx = __builtin_ctz(b.bx), sy = __builtin_ctz(b.by);
+  const uint16_t* ul = ulist + (int64_t)gb * (b.bx * b.by * b.bt);
+  for (int r = threadIdx.x & 63; r < q; r += 64) {
+    const int li = ul[r];
+    const int x = bxi * b.bx + (li & (b.bx - 1)), y = byi * b.by + ((li >> sx) & (b.by - 1)),
+              t = bti * b.bt + (li >> (sx + sy));
+    srow[first + r] = make_int2(si, (t * s.H + y) * s.W + x);
   }
 }
 
@@ -835,14 +893,31 @@ static void launch_brick_scan(const Batch& bt, const Workspace& w, int nb, int c
   }
   hipLaunchKernelGGL(k_scan_totals, dim3(ntiles), dim3(kScanThreads), 0, s, w.brick_nq, nb, ch,
                      sr.sp, w.scan_part);
-  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanThreads), 0, s, ntiles, nb, sr.rs,
-                     w.scan_part, w.brick_off, order, w.plan);
+  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanThreads), 0, s, ntiles, nb, sr, w.scan_part,
+                     w.brick_off, w.plan);
   if (sr.sp > 0)
     hipLaunchKernelGGL((k_scan_place<false, true>), dim3(ntiles), dim3(kScanThreads), 0, s, bt,
                        w.brick_nq, nb, ch, sr, w.scan_part, w.brick_off, order, w.plan);
   else
     hipLaunchKernelGGL((k_scan_place<false, false>), dim3(ntiles), dim3(kScanThreads), 0, s, bt,
                        w.brick_nq, nb, ch, sr, w.scan_part, w.brick_off, order, w.plan);
+}
+
+// The scan, then the list of single rows.
+static void launch_work_list(const Batch& bt, const Workspace& w, const EncodeTables& et,
+                             int num_cus, bool single, hipStream_t s) {
+  SparseRows sr;
+  if (single && et.sp > 0) {
+    // (calls of at most a full item per CU: every brick of less than one chunk)
+    sr.sp = (int64_t)bt.m <= (int64_t)et.rs * num_cus ? std::max(et.sp, et.rs + 1) : et.sp;
+    sr.rs = et.rs;
+    sr.cus = num_cus;
+  }
+  launch_brick_scan(bt, w, bt.nbricks, encode_rows_per_chunk(et.d, et.layout), sr, s);
+  if (sr.sp > 0)
+    hipLaunchKernelGGL(k_list_rows, dim3((bt.nbricks + 3) / 4), dim3(256), 0, s, bt, et.brick,
+                       sr.sp, w.brick_nq, w.brick_off, ulist_of(w), w.plan,
+                       reinterpret_cast<int2*>(w.srow));
 }
 
 // The row of slice-local voxel v (a query voxel of slice s).
@@ -1018,7 +1093,7 @@ static void launch_rank(const Batch& bt, const Workspace& w, const Brick& b, boo
   const bool big = b.volume() > 4096;
   auto go = [&](auto fn) {
     hipLaunchKernelGGL(fn, dim3(bt.nbricks), dim3(256), 0, s, bt, b, w.count, w.qmark, w.rank,
-                       w.ulist, w.brick_nq);
+                       ulist_of(w), w.brick_nq);
   };
   if (all)
     big ? go(k_rank<true, 32>) : go(k_rank<true, 16>);
@@ -1032,11 +1107,13 @@ static void launch_rank_lines(const Batch& bt, const Workspace& w, const Brick& 
   // sparse bricks)
   auto go = [&](auto fn, unsigned blocks, size_t lds) {
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(256), lds, s, bt, b, w.count, w.lines, w.qmark,
-                       w.rank, w.ulist, w.brick_nq, w.pairs, w.err);
+                       w.rank, ulist_of(w), w.brick_nq, w.pairs,
+                       reinterpret_cast<uint2*>(brick_bits(w)), w.err);
   };
   auto go8 = [&](auto fn, unsigned blocks) {
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(512), 0, s, bt, b, w.count, w.lines, w.qmark,
-                       w.rank, w.ulist, w.brick_nq, w.pairs, w.err);
+                       w.rank, ulist_of(w), w.brick_nq, w.pairs,
+                       reinterpret_cast<uint2*>(brick_bits(w)), w.err);
   };
   const unsigned nb = (unsigned)bt.nbricks, nb4 = (unsigned)((bt.nbricks + 3) / 4);
   const size_t rows_lds = 4 * (size_t)b.by * b.bt * sizeof(uint16_t);  // (at most 16 KiB)
@@ -1074,7 +1151,8 @@ int launch_clear_grids(const Batch& bt, const Workspace& w, int64_t nlines, void
 }
 
 int launch_prepare(const Batch& bt, const Workspace& w, const veckm_event* ev,
-                   const int32_t* queries, const EncodeTables& et, bool pairs, void* stream) {
+                   const int32_t* queries, const EncodeTables& et, bool pairs, int num_cus,
+                   void* stream) {
   hipStream_t s = (hipStream_t)stream;
   // (a brick has at most kMaxBrickVoxels / 4 rows of flags; a step of the
   // ranking kernels holds whole rows)
@@ -1097,17 +1175,7 @@ int launch_prepare(const Batch& bt, const Workspace& w, const veckm_event* ev,
     launch_rank_lines(bt, w, et.brick, queries == nullptr, s);
   else
     launch_rank(bt, w, et.brick, queries == nullptr, s);
-  // single rows, unless every brick is likely to hold many (a dense call
-  // with 32 or more rows per brick on average)
-  SparseRows sr;
-  if (pairs && et.sp > 0 && !(dense_batch(bt) && (int64_t)bt.m >= 32 * (int64_t)bt.nbricks)) {
-    sr.sp = et.sp;
-    sr.rs = et.rs;
-    sr.bv = et.brick.volume();
-    sr.ulist = w.ulist;
-    sr.srow = reinterpret_cast<int2*>(w.srow);
-  }
-  launch_brick_scan(bt, w, bt.nbricks, encode_rows_per_chunk(et.d, et.layout), sr, s);
+  launch_work_list(bt, w, et, num_cus, pairs, s);
   // the paper form needs each row's voxel (and its expansion reads the query
   // -> row map); the other forms find rows as they expand
   if (!pairs && bt.m > 0)
@@ -1148,7 +1216,7 @@ int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, int
 }
 
 int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event* queries,
-                          const EncodeTables& et, void* stream) {
+                          const EncodeTables& et, int num_cus, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   if (bt.n > 0) {
     // locate the query events and mark their voxels in one pass
@@ -1157,7 +1225,7 @@ int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event
                        et.brick, (uint8_t*)nullptr);
   }
   launch_rank(bt, w, et.brick, false, s);
-  launch_brick_scan(bt, w, bt.nbricks, encode_rows_per_chunk(et.d, et.layout), SparseRows{}, s);
+  launch_work_list(bt, w, et, num_cus, false, s);  // (a window's rows have no bits: bricks only)
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
 

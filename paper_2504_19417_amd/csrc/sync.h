@@ -50,5 +50,10 @@ __device__ inline void copy_to_lds4(const void* src, uint32_t lds_base) {
   asm volatile("s_nop 4\n\tglobal_load_lds_dword %0, off"
                :: "v"(src), "{m0}"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
 }
+// (masked-off lanes copy nothing; the others' places do not move)
+__device__ inline void copy_to_lds4_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_nop 4\n\tglobal_load_lds_dword %0, %1"
+               :: "v"(voff), "s"(sbase), "{m0}"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
+}
 
 }  // namespace veckm

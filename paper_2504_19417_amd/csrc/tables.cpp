@@ -175,12 +175,20 @@ SlotTable make_slots(int rx, int ry, int rt) {
 std::vector<uint16_t> make_slot_fragments(const SlotTable& t, const double* A, int d, int na) {
   const int nt_total = d / 16, ksteps = t.KP / kKStep;
   std::vector<uint16_t> frag((size_t)ksteps * na * nt_total * 64 * 8, 0);
-  size_t idx = 0;
+  // a slab's fragments in the order the encoder moves and reads them
+  // (slab_fragment in encode_kernel.h): two halves of every array from D = 64 on
+  const int hn = nt_total >= 8 ? 4 : 2, wn = nt_total / (2 * hn);
+  auto place = [&](int a, int nt) {
+    return nt_total < 4 ? a * nt_total + nt
+                        : (((nt / hn) % 2 * na + a) * wn + nt / (2 * hn)) * hn + nt % hn;
+  };
   for (int ks = 0; ks < ksteps; ++ks)
     for (int a = 0; a < na; ++a)
       for (int nt = 0; nt < nt_total; ++nt)
         for (int lane = 0; lane < 64; ++lane)
-          for (int e = 0; e < 8; ++e, ++idx) {
+          for (int e = 0; e < 8; ++e) {
+            const size_t idx =
+                ((((size_t)ks * na * nt_total + place(a, nt)) * 64) + lane) * 8 + e;
             const int k = ks * kKStep + 8 * (lane >> 4) + e;
             const int j = 16 * nt + (lane & 15);
             const int* s = &t.slot[4 * k];
@@ -206,6 +214,16 @@ std::vector<int32_t> make_run_offsets(const SlotTable& t, const Brick& b, int rx
   for (int r = 0; r < t.KP / 4; ++r) {
     const int* s = &t.slot[4 * 4 * r];
     runs[r] = (s[2] * SY + s[1]) * SX + s[0];
+  }
+  return runs;
+}
+
+std::vector<int32_t> make_run_triples(const SlotTable& t) {
+  static_assert(kMaxRxy + kRunPad < 32, "packed run offsets");
+  std::vector<int32_t> runs(t.KP / 4, 0);
+  for (int r = 0; r < t.KP / 4; ++r) {
+    const int* s = &t.slot[4 * 4 * r];
+    runs[r] = (s[0] + 32) | (s[1] + 32) << 8 | s[2] << 16;
   }
   return runs;
 }
@@ -308,13 +326,12 @@ std::vector<Tiling> tiling_candidates(int rx, int ry, int rt, int d, int precisi
       out.push_back(t);
     }
   // where the encoder can run the perceptron itself (D = 64 or 128), the
-  // 16-wave pipelined layout on the default brick comes first: the fused
-  // perceptron keeps rows out of HBM, and on the 1M-event slice it runs
-  // the FP32 form as fast as the 8-wave layout (0.46 ms after warm-up) and
-  // the FP16 form's larger bricks about 4 % faster (0.31 against 0.32 ms;
-  // the tuner picks those bricks when slices are long enough for them).
+  // 8-wave pipelined layout on the default brick comes first: the fused
+  // perceptron keeps rows out of HBM, and two row tiles per wave halve the
+  // table fragments read from LDS (1M-event slice, whole call: FP32 form 0.55
+  // against 0.61 ms for 16 waves of one tile, FP16 form 0.36 against 0.44 ms).
   if (d == 64 || d == 128) {
-    const int want = 4;
+    const int want = 3;
     long pick = -1;
     for (size_t k = 1; k < out.size() && pick < 0; ++k) {
       const Tiling& t = out[k];
@@ -340,7 +357,7 @@ std::vector<uint16_t> make_w1_fragments(const float* W1, int hidden, int d, int 
       for (int kk = 0; kk < nt; ++kk)
         for (int lane = 0; lane < 64; ++lane)
           for (int e = 0; e < 8; ++e, ++idx) {
-            const int t = q / 2, tile = q % 2;
+            const int tile = q / terms, t = q % terms;  // a hidden tile per half slab
             const int h = (2 * ms + tile) * 16 + (lane & 15);
             const int g = lane >> 4;
             // feature: tile 2kk' (e < 4) or 2kk' + 1 (e >= 4) of the real

@@ -51,6 +51,9 @@ std::vector<uint16_t> make_slot_fragments(const SlotTable& t, const double* A, i
 // LDS voxel-index delta of the first slot of every run, laid out
 // [ks][lane group][2].
 std::vector<int32_t> make_run_offsets(const SlotTable& t, const Brick& b, int rx, int ry);
+// First offset of every run in the same order, packed: (dx + 32) | (dy + 32)
+// << 8 | dt << 16 (radii are at most kMaxRxy, dt >= 0).
+std::vector<int32_t> make_run_triples(const SlotTable& t);
 // fp16 bit patterns of the neighbour-count weight of every slot (1 for an
 // offset, 1/2 for the centre, 0 for padding).
 std::vector<uint16_t> make_slot_weights(const SlotTable& t);
@@ -70,13 +73,19 @@ constexpr int kMaxBrickVoxels = 8192;  // largest brick (the ranking kernel's li
 // Work items of the encoder that hold single rows carry this bit in their
 // brick field (brick numbers stay below it).
 constexpr int kSparseTag = 1 << 30;
-// Bricks with fewer rows than this go to the encoder row by row (each row
-// with its own count box, up to 16 rows per item), when 8 or more such
-// boxes fit in the LDS of the brick's box.
-constexpr int kSparseBelow = 12;
+// Bricks with fewer rows than this go to the encoder row by row.  A full chunk
+// of single rows costs about 1.2 of a brick's, a brick's chunk costs its box
+// and the better part of a full chunk's time however few rows it holds.  Whole
+// call with 64 / 128 / 192: 64 lognormal slices 5.33 / 4.90 / 4.95 ms, 5M-event
+// slice 2.71 / 2.68 / 2.78 ms, 50k events encoded 0.140 / 0.124 / 0.123 ms.
+constexpr int kSparseBelow = 128;
 std::vector<Tiling> tiling_candidates(int rx, int ry, int rt, int d, int precision, int kp);
 size_t encode_lds_need(int d, int precision, int nbuf, int kp, int vol, int layout = 0);
 int encode_rows_per_chunk(int d, int layout);
+struct EncodeTables;
+// Single rows the encoder takes per item at most (a chunk whose row records
+// fit in the space of the brick's box).
+int encode_single_rows(const EncodeTables& et);
 int encode_waves(int layout = 0);  // waves per encoder block
 int lds_volume_halves(const Brick& b, int rx, int ry, int rt);
 // The encoder's LDS box of a brick: the brick plus the window halo, widened
@@ -139,20 +148,25 @@ struct Workspace {
   int32_t* rank = nullptr;      // voxels: brick-local rank of query voxels
   uint8_t* qmark = nullptr;     // voxels: query-voxel marks (query subsets, windows); all zero
                                 // between calls (the ranking pass clears the marks it reads)
-  int32_t* ulist = nullptr;     // bricks * brick volume: brick-local voxel of each rank
+  int32_t* ulist = nullptr;     // 2 bytes per brick voxel (umax in all): the brick-local voxel of
+                                // each rank; then, in as many bytes again, the brick x rows'
+                                // bits (brick_bits)
   int32_t* brick_nq = nullptr;  // bricks
   int32_t* brick_off = nullptr; // bricks + 1 (exclusive scan)
   int32_t* order = nullptr;     // 4 x bricks: the encoder's work list, most chunks first;
                                 // per brick {brick, rows, first row, slice}
   int32_t* scan_part = nullptr; // kScanNV ints per kScanTile bricks (brick-scan partials)
-  int32_t* srow = nullptr;      // 2 U: {brick, brick-local voxel} of each row of the bricks the
+  int32_t* srow = nullptr;      // 2 U: {slice, slice-local voxel} of each row of the bricks the
                                 // encoder takes row by row (numbered after all other rows)
   int32_t* vox = nullptr;       // n: slice-local voxel of each event, -1 if invalid
   int32_t* qmap = nullptr;      // m: row of each query, -1 if invalid
   int32_t* rowvox = nullptr;    // U: voxel of each row (paper form only)
   void* rows = nullptr;         // U x 2D encodings (fp32 or bf16)
   float* rowflow = nullptr;     // U x 2
-  int32_t* plan = nullptr;      // [0] = U, [1] = work counter, [2] = non-empty bricks
+  int32_t* plan = nullptr;      // [0] = U, [1] = work counter, [2] = work items, [3] = rows of
+                                // whole bricks (single rows follow), [4] = whole bricks, [5] =
+                                // single rows per item, [6] = bricks of several chunks (the
+                                // single rows' items come after them)
   int32_t* err = nullptr;       // error bits
   int64_t vmax = 0, pmax = 0, nmax = 0, bmax = 0, umax = 0;
   // paper form (no temporal bound) only
@@ -162,6 +176,16 @@ struct Workspace {
   int32_t* nbx = nullptr;       // [H][W] x box sums of cnt2
   int32_t* nbox = nullptr;      // [H][W] window counts
 };
+
+// The brick-local voxels of each brick's ranks (bricks x brick volume).
+inline uint16_t* ulist_of(const Workspace& w) { return reinterpret_cast<uint16_t*>(w.ulist); }
+// Per brick x row of a bounded-window slice call (bricks x (by bt), bx <= 32):
+// two words, bit x of which are the low and the high bit of voxel x's count (3
+// for 3 and more events).  (8 bytes per bx >= 4 voxels: within the 2 bytes
+// per voxel behind the lists.)  Written whole by the ranking kernels.
+inline uint32_t* brick_bits(const Workspace& w) {
+  return reinterpret_cast<uint32_t*>(ulist_of(w) + w.umax);
+}
 
 // Phase tables of the paper form: (cos, sin) of A_t[j] t for the bins of a
 // slice, of A_x[j] x over the sensor columns and of A_y[j] y over its rows
@@ -176,10 +200,10 @@ struct PaperTables {
 struct EncodeTables {
   const uint16_t* frag = nullptr;  // fragment-native phase table over the slots
   const int32_t* runs = nullptr;   // KP / 4 run byte offsets
-  const int32_t* runs1 = nullptr;  // the same for the count box of a single voxel
+  const int32_t* runs1 = nullptr;  // KP / 4 packed run offsets (single rows)
   // bricks with fewer than sp rows (0: none) go to the encoder row by row, in
-  // items of up to rs rows with a count box each
-  int sp = 0, rs = 1;
+  // items of up to rs rows
+  int sp = 0, rs = 16;
   const uint16_t* wts = nullptr;   // KP slot weights (fp16)
   int K = 0, KP = 0, na = 4;
   int nbuf = 3;  // k-step slabs of the table buffered in LDS (2 to 4)
@@ -220,11 +244,11 @@ struct MlpWeights {
 // Widest perceptron hidden layer a context accepts.
 constexpr int kMaxHidden = 512;
 
-// W1 laid out as table slabs of the fused encoder (layout 2, WN = 1): slab s
-// holds hidden tiles 2s and 2s + 1 (16 units each) for every 32-feature step
-// kk of layer 1, fragment (t * 2 + tile, kk) as the MFMA A operand (64 lanes
-// x 8 halves; t = 0 for the bf16 or fp16-hi term, 1 for the fp16-lo term of
-// W1 * 2^shift).  Feature order within a step matches the encoder's
+// W1 laid out as table slabs of the fused encoder (WN = 1): slab s holds
+// hidden tiles 2s and 2s + 1 (16 units each), a tile per half slab, for every
+// 32-feature step kk of layer 1: fragment (tile, t, kk) as the MFMA A operand
+// (64 lanes x 8 halves; t = 0 for the bf16 or fp16-hi term, 1 for the fp16-lo
+// term of W1 * 2^shift).  Feature order within a step matches the encoder's
 // accumulator layout (frequency tiles 2kk' and 2kk' + 1 of the real parts
 // for kk < D / 32, of the imaginary parts above).
 std::vector<uint16_t> make_w1_fragments(const float* W1, int hidden, int d, int na, int shift);
@@ -232,7 +256,8 @@ std::vector<uint16_t> make_w1_fragments(const float* W1, int hidden, int d, int 
 bool encode_fusable(const EncodeTables& et, int hidden);
 
 int launch_prepare(const Batch& bt, const Workspace& w, const veckm_event* ev,
-                   const int32_t* queries, const EncodeTables& et, bool pairs, void* stream);
+                   const int32_t* queries, const EncodeTables& et, bool pairs, int num_cus,
+                   void* stream);
 int launch_paper_encode(const Batch& bt, const Workspace& w, const PaperTables& pt,
                         const Brick& brick, int rows, int num_cus, void* stream);
 // (cos, sin) tables of the paper form, FP64 then rounded to fp32: time bins
@@ -268,9 +293,7 @@ int launch_expand_count(const Batch& bt, const Workspace& w, const int32_t* quer
 // Whether a bounded-window slice call is dense: its count and pair grids
 // hold fewer than 30 entries per event.  Dense calls clear the two grids
 // with one pass over them (about 1.5 GB/ms against about 50 M events/ms for
-// per-event stores) and rank a brick per block; with 32 or more rows per
-// brick on average they also take every non-empty brick whole in the
-// encoder (no single rows).
+// per-event stores) and rank a brick per block.
 inline bool dense_batch(const Batch& bt) { return bt.nvox + bt.npairs < 30 * (int64_t)bt.n; }
 // After a bounded-window slice call whose launches all went through: the
 // counts and pair entries of its events' voxels back to zero (the ranking
@@ -288,7 +311,7 @@ int launch_take_err(const Workspace& w, int32_t* host, void* stream);
 int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, int W, int H, int T,
                        int t0, int nbins, int tref, int64_t clear_b0, int clear_nb, void* stream);
 int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event* queries,
-                          const EncodeTables& et, void* stream);
+                          const EncodeTables& et, int num_cus, void* stream);
 
 // ------------------------------------------------------------ perceptron training
 constexpr int kTrainBlockRows = 256;  // most rows a block of the forward kernel takes
