@@ -1101,6 +1101,13 @@ static void launch_rank(const Batch& bt, const Workspace& w, const Brick& b, boo
     big ? go(k_rank<false, 32>) : go(k_rank<false, 16>);
 }
 
+// Small calls whose bricks hold some rows also rank a brick per block, of 8
+// waves: all blocks run at once, and a wave visits one group of voxel steps
+// instead of up to eight in turn.  20k events in 748 bricks: the whole call
+// 71.7 to 59.9 us; 500 events in 187 bricks (one group per brick at most) are
+// better off with a wave each, 46.6 against 48.8 us.
+constexpr int kBlockBricks = 2048, kBlockEvents = 8;
+
 static void launch_rank_lines(const Batch& bt, const Workspace& w, const Brick& b, bool all,
                               hipStream_t s) {
   // dense calls: a block per brick; else a wave per brick (latency-bound
@@ -1117,10 +1124,12 @@ static void launch_rank_lines(const Batch& bt, const Workspace& w, const Brick& 
   };
   const unsigned nb = (unsigned)bt.nbricks, nb4 = (unsigned)((bt.nbricks + 3) / 4);
   const size_t rows_lds = 4 * (size_t)b.by * b.bt * sizeof(uint16_t);  // (at most 16 KiB)
-  if (dense_batch(bt)) {
+  const bool spread = !dense_batch(bt) && bt.nbricks <= kBlockBricks &&
+                      (int64_t)bt.n >= kBlockEvents * (int64_t)bt.nbricks;
+  if (dense_batch(bt) || spread) {
     // (8 waves for the largest bricks: with a quarter of the blocks, 4 waves
     // each left the kernel latency-bound)
-    if (b.volume() > 4096)
+    if (b.volume() > 4096 || spread)
       all ? go8(k_rank_lines4<true, 8>, nb) : go8(k_rank_lines4<false, 8>, nb);
     else
       all ? go(k_rank_lines4<true, 4>, nb, 0) : go(k_rank_lines4<false, 4>, nb, 0);
