@@ -75,13 +75,14 @@ struct veckm_ctx {
   Workspace w;
   MlpWeights mw;
   bool paper = false;  // no temporal bound: the staged 2-D pooling encoder
-  // sliding window (veckm_window_*): the count and pair grids are a ring of
+  // sliding window (veckm_window_*): the count and pair grids and the bits are a ring of
   // max_bins planes holding bins [wend - max_bins, wend); bin t sits in plane
   // (t - tref) mod max_bins
   bool window = false;
   bool started = false;
   int32_t tref = 0;
   int64_t wend = 0;
+  int bits_tiling = 0;  // the tiling whose order the ring's bits lie in
   PaperTables pt;
   int max_slices = 1;
   std::vector<void*> allocs;
@@ -185,7 +186,7 @@ int64_t bytes_for(const veckm_params* p, const std::vector<Tiling>& tl, int kp, 
     bytes += 2 * 2 * (int64_t)p->d * V2 * 4 + 3 * V2 * 4 + s.U * 4;
     bytes += (int64_t)(p->max_bins + p->width + p->height) * p->d * 8;
   }
-  bytes += s.V * (4 + 4 + 1);                     // count, rank, qmark
+  bytes += s.V * (4 + 4 + 1) + 2 * kGridPad * 4;  // count, rank, qmark
   if (p->rt >= 0) bytes += s.P * 4 + s.lines;     // pair grid, brick row flags
   bytes += s.ulist * 4;                           // ulist
   bytes += (6 * s.nb + 1) * 4;                    // brick_nq, brick_off, order
@@ -195,7 +196,7 @@ int64_t bytes_for(const veckm_params* p, const std::vector<Tiling>& tl, int kp, 
   bytes += s.U * 2 * p->d * 4 + s.U * 8;          // rows (fp32 size), rowflow
   bytes += (int64_t)kp * p->d * na * 2 + kp * 2;  // phase table, weights
   bytes += (int64_t)tl.size() * kp;               // run offsets (one table per tiling)
-  bytes += 64 * 4 + 4 + 64 * 4;                   // plan, err, zero page
+  bytes += 64 * 4 + 4;                            // plan, err
   bytes += (int64_t)kRing * slices_of(p) * (int64_t)sizeof(SliceDesc);  // slice tables
   bytes += (int64_t)hidden * (2 * p->d) * 10 + hidden * 12 + 8;  // perceptron (fp32, bf16, fp16 hi/lo W1)
   if (p->rt >= 0 && (p->d == 64 || p->d == 128))  // room for W1 after the phase table
@@ -562,7 +563,6 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
   uint16_t* dfrag = nullptr;
   std::vector<int32_t*> druns(tl.size(), nullptr);
   uint16_t* dwts = nullptr;
-  uint32_t* dzeros = nullptr;
   float* rows = nullptr;
   rc = VECKM_OK;
   // the phase table's slabs, then room for W1 in the same slab order (the
@@ -576,8 +576,8 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
   c->w1_slot = fusable && !rc ? dfrag + frag.size() : nullptr;
   for (size_t i = 0; i < tl.size(); ++i) rc = rc ? rc : dalloc(c->allocs, &druns[i], st.KP / 4);
   rc = rc ? rc : dalloc(c->allocs, &dwts, wts.size());
-  rc = rc ? rc : dalloc(c->allocs, &dzeros, 64);
-  rc = rc ? rc : dalloc(c->allocs, &w.count, (size_t)s.V);
+  rc = rc ? rc : dalloc(c->allocs, &w.count, (size_t)s.V + 2 * kGridPad);
+  if (!rc) w.count += kGridPad;
   if (!c->paper) rc = rc ? rc : dalloc(c->allocs, &w.pairs, (size_t)s.P);
   if (!c->paper) rc = rc ? rc : dalloc(c->allocs, &w.lines, (size_t)s.lines);
   rc = rc ? rc : dalloc(c->allocs, &w.rank, (size_t)s.V);
@@ -648,13 +648,11 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
   }
   if (!rc && hipMemcpy(dwts, wts.data(), wts.size() * 2, hipMemcpyHostToDevice) != hipSuccess)
     rc = VECKM_E_HIP;
-  if (!rc && hipMemset(dzeros, 0, 64 * sizeof(uint32_t)) != hipSuccess) rc = VECKM_E_HIP;
   if (!rc && hipMemset(w.err, 0, sizeof(int32_t)) != hipSuccess) rc = VECKM_E_HIP;
   if (!rc && hipMemset(w.qmark, 0, (size_t)s.V) != hipSuccess) rc = VECKM_E_HIP;
   if (!rc && hipMemset(w.count, 0, (size_t)s.V * 4) != hipSuccess) rc = VECKM_E_HIP;
   if (!rc && !c->paper &&
-      (hipMemset(w.pairs, 0, (size_t)s.P * 4) != hipSuccess ||
-       hipMemset(w.lines, 0, (size_t)s.lines) != hipSuccess))
+      hipMemset(w.lines, 0, (size_t)s.lines) != hipSuccess)
     rc = VECKM_E_HIP;
   if (!rc && hipMemset(w.plan, 0, 64 * sizeof(int32_t)) != hipSuccess) rc = VECKM_E_HIP;
   if (!rc && hipDeviceSynchronize() != hipSuccess) rc = VECKM_E_HIP;
@@ -663,7 +661,6 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
     return rc;
   }
   w.rows = rows;
-  w.zeros = dzeros;
   w.vmax = s.V;
   w.pmax = s.P;
   w.nmax = s.n;
@@ -803,17 +800,26 @@ int veckm_window_create(const veckm_params* params, veckm_ctx** out) {
   int rc = veckm_create(params, &c);
   if (rc) return rc;
   c->window = true;
-  // an empty window: every plane of the ring holds zero counts
+  // an empty window: every plane of the ring holds zero counts (and bits, in
+  // any tiling's order)
   const int64_t V = (int64_t)params->width * params->height * params->max_bins;
-  const int64_t P = (int64_t)(params->width + 1) * params->height * params->max_bins;
   if (hipMemset(c->w.count, 0, (size_t)V * 4) != hipSuccess ||
-      hipMemset(c->w.pairs, 0, (size_t)P * 4) != hipSuccess ||
+      hipMemset(c->w.ulist, 0, (size_t)c->w.umax * 4) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
     veckm_destroy(c);
     return VECKM_E_HIP;
   }
   *out = c;
   return VECKM_OK;
+}
+
+// The ring's bits lie in the order of the tiling in use: rebuilt whole after
+// another one was selected.
+static int window_bits(veckm_ctx* c, const Batch& bt, void* stream) {
+  if (c->bits_tiling == c->tiling) return VECKM_OK;
+  const int rc = launch_window_bits(c->w, bt, c->et.brick, 0, c->p.max_bins, stream);
+  if (!rc) c->bits_tiling = c->tiling;
+  return rc;
 }
 
 int veckm_window_push(veckm_ctx* ctx, const veckm_event* events, int64_t n, int32_t t0,
@@ -827,8 +833,11 @@ int veckm_window_push(veckm_ctx* ctx, const veckm_event* events, int64_t n, int3
   const int64_t wend0 = ctx->started ? ctx->wend : (int64_t)t0;
   const int64_t end = (int64_t)t0 + nbins;
   const int64_t b0 = end - T > wend0 ? end - T : wend0;  // bins entering the window
-  const int rc = launch_window_push(ctx->w, events, n, ctx->p.width, ctx->p.height, T, t0, nbins,
-                                    tref, b0, (int)(end - b0), stream);
+  Batch bt{};
+  bt.s0 = describe(ctx, ctx->p.width, ctx->p.height, T, 0, 0, 0, 0, 0, n);
+  int rc = launch_window_push(ctx->w, events, n, bt, ctx->et.brick, t0, nbins, tref, b0,
+                              (int)(end - b0), stream);
+  if (!rc) rc = window_bits(ctx, bt, stream);
   if (rc) return rc;
   ctx->started = true;
   ctx->tref = tref;
@@ -864,7 +873,8 @@ int window_batch(veckm_ctx* c, const veckm_event* queries, int64_t m, const void
 int veckm_window_encode(veckm_ctx* ctx, const veckm_event* queries, int64_t m, float* emb,
                         void* stream) {
   Batch bt;
-  const int rc = window_batch(ctx, queries, m, emb, &bt);
+  int rc = window_batch(ctx, queries, m, emb, &bt);
+  if (!rc) rc = window_bits(ctx, bt, stream);
   if (rc) return rc;
   return run(ctx, ctx->w, bt, queries, nullptr, emb, nullptr, stream);
 }
@@ -872,9 +882,11 @@ int veckm_window_encode(veckm_ctx* ctx, const veckm_event* queries, int64_t m, f
 int veckm_window_flow(veckm_ctx* ctx, const veckm_event* queries, int64_t m, float* flow,
                       void* stream) {
   Batch bt;
-  const int rc = window_batch(ctx, queries, m, flow, &bt);
+  int rc = window_batch(ctx, queries, m, flow, &bt);
   if (rc) return rc;
   if (ctx->mw.hidden == 0) return VECKM_E_STATE;
+  rc = window_bits(ctx, bt, stream);
+  if (rc) return rc;
   return run(ctx, ctx->w, bt, queries, nullptr, nullptr, flow, stream);
 }
 
@@ -1166,8 +1178,10 @@ int64_t carve_noalloc(const veckm_ctx* c, const Batch& bt, unsigned char* base, 
     off += (bytes + 255) / 256 * 256;
     return p;
   };
-  w->count = reinterpret_cast<int32_t*>(take(V * 4));
+  // (the count grid between two others: kGridPad voxels around it are memory)
+  static_assert(kGridPad * 4 <= 256, "arrays are padded to 256 bytes");
   w->pairs = reinterpret_cast<uint32_t*>(take(P * 4));
+  w->count = reinterpret_cast<int32_t*>(take(V * 4));
   w->lines = take(nb * b.by * b.bt);
   w->rank = reinterpret_cast<int32_t*>(take(V * 4));
   w->qmark = nullptr;  // read only for query subsets

@@ -62,8 +62,8 @@ struct EncArgs {
   const uint4* frag;     // the phase table's slabs, then W1's (hidden / 32, make_w1_fragments)
   const int32_t* runs;
   const uint16_t* wts;
+  const int32_t* count;
   const uint32_t* pairs;
-  const uint32_t* zeros;
   void* rows;
   int32_t* plan;
   int32_t* rowcnt;  // per-row neighbour counts, or NULL
@@ -80,6 +80,9 @@ struct EncArgs {
 // Dwords of a single row's bits: 16 per run, padded to an odd multiple of 4
 // dwords so that the 16 rows of a tile read from different banks.
 constexpr int kLutDwords = 512;
+// Plane number of rows without a ring: no step of up to kMaxRt planes leaves
+// [0, 2 kNoRing).
+constexpr int kNoRing = 1 << 14;
 __host__ __device__ constexpr int single_row_dwords(int nsteps) { return (nsteps | 1) * 4; }
 
 __host__ __device__ constexpr bool fused_rows(int rows) { return rows == kFlowBF16 || rows == kFlowHiLo16; }
@@ -231,9 +234,10 @@ typedef __attribute__((address_space(3))) uintx4 lds_uint4;
 struct RowRefs {
   const lds_u32* bits;   // two runs (a lane's share of a k-step) per dword
   int stride;            // dwords from tile to tile
-  const lds_uint4* head; // per row: address of its pair-grid entry (64 bits), entries per x row
-  int hstride;           // and per plane
+  const lds_uint4* head; // per row: address of its pair-grid entry (48 bits), its plane, entries
+  int hstride;           // per x row and per plane
   const lds_uint2* lut;  // a run's 8 bits -> its pair dwords
+  int planes;            // of the ring (more than any plane number without one)
 };
 
 typedef __attribute__((address_space(1))) uint32_t global_u32;
@@ -311,18 +315,22 @@ struct CountWords {
       const uint32_t many = w & (w >> 4) & 0x0f0f0f0fu;
       if (__any(many != 0)) {
         const uintx4 head = rr.head[mt * rr.hstride];
-        const global_u32* base = (const global_u32*)((uint64_t)head.y << 32 | head.x);
+        const global_u32* base =
+            (const global_u32*)((uint64_t)(head.y & 0xffffu) << 32 | head.x);
+        const int plane = (int)(head.y >> 16);
         const int2 ro = runs[at];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int r = u ? ro.y : ro.x;
           const int dx = (r & 255) - 32, dy = ((r >> 8) & 255) - 32, dt = r >> 16;
-          const int off = dt * (int)head.w + dy * (int)head.z + dx;
+          const int d = dy * (int)head.z + dx, hw = (int)head.w;
+          const int p = d + (plane + dt >= rr.planes ? dt - rr.planes : dt) * hw;
+          const int q = -d + (plane - dt < 0 ? rr.planes - dt : -dt) * hw;
           const uint32_t m = many >> (16 * u);
-          if (m & 0x003) P[mt][2 * u] = base[off];
-          if (m & 0x00c) P[mt][2 * u + 1] = base[off + 2];
-          if (m & 0xc00) Q[mt][2 * u] = base[-off - 1];
-          if (m & 0x300) Q[mt][2 * u + 1] = base[-off - 3];
+          if (m & 0x003) P[mt][2 * u] = base[p];
+          if (m & 0x00c) P[mt][2 * u + 1] = base[p + 2];
+          if (m & 0xc00) Q[mt][2 * u] = base[q - 1];
+          if (m & 0x300) Q[mt][2 * u + 1] = base[q - 3];
         }
       }
     }
@@ -1014,6 +1022,8 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         const SliceDesc sl =
             a.bt.nslices == 1 ? a.bt.s0 : a.lds_slices ? stab[e.x] : a.bt.table[e.x];
         const int x = e.y % sl.W, yt = e.y / sl.W, y = yt % sl.H, t = yt / sl.H;
+        const bool ring = sl.tshift != 0;  // (bin t sits in plane t + tshift, wrapped)
+        const int tp = t + sl.tshift < sl.T ? t + sl.tshift : t + sl.tshift - sl.T;
         uint32_t* rb = rbits + r * rstride;
         uint16_t* out = reinterpret_cast<uint16_t*>(rb);
         const int nl = a.b.by * a.b.bt, sx = __builtin_ctz(a.b.bx), sy = __builtin_ctz(a.b.by),
@@ -1023,16 +1033,16 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         if (part == 0) {
           const int w1 = sl.W + 1;
           const uint64_t at = reinterpret_cast<uint64_t>(
-              a.pairs + sl.pair_off + ((int64_t)t * sl.H + y) * w1 + (x + 1));
-          heads[r] = make_uint4((uint32_t)at, (uint32_t)(at >> 32), (uint32_t)w1,
-                                (uint32_t)(w1 * sl.H));
+              a.pairs + sl.pair_off + ((int64_t)tp * sl.H + y) * w1 + (x + 1));
+          heads[r] = make_uint4((uint32_t)at, (uint32_t)(at >> 32) | (uint32_t)(ring ? tp : kNoRing) << 16,
+                                (uint32_t)w1, (uint32_t)(w1 * sl.H));
           for (int k = nc + (nwr - 1) * nr; k < a.nsteps * 8; ++k) out[k] = 0;  // padding runs
         }
         // The words of the window row at (y + dy, t + dt), brick column cx.  The
         // address is the row's own brick's plus 24-bit steps of bricks, columns
         // and x rows; outside the slice any word is read and masked (no branch,
         // so that loads are not serialised).
-        const int tb = t >> stt, yb = y >> sy, xb = x >> sx, plane = sl.nbx * sl.nby;
+        const int tb = tp >> stt, yb = y >> sy, xb = x >> sx, plane = sl.nbx * sl.nby;
         const uint2* own = a.bits + (int64_t)(sl.brick_off + (tb * sl.nby + yb) * sl.nbx + xb) * nl;
         struct Line {
           int off;
@@ -1040,8 +1050,9 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         };
         auto line = [&](int dy, int dt) -> Line {
           const int yy = y + dy, tt = t + dt;
-          const int step = __mul24((tt >> stt) - tb, plane) + __mul24((yy >> sy) - yb, sl.nbx);
-          return {(step << (sy + stt)) + ((tt & (a.b.bt - 1)) << sy) + (yy & (a.b.by - 1)),
+          const int pl = tt + sl.tshift < sl.T ? tt + sl.tshift : tt + sl.tshift - sl.T;
+          const int step = __mul24((pl >> stt) - tb, plane) + __mul24((yy >> sy) - yb, sl.nbx);
+          return {(step << (sy + stt)) + ((pl & (a.b.bt - 1)) << sy) + (yy & (a.b.by - 1)),
                   (bool)(((unsigned)yy < (unsigned)sl.H) & ((unsigned)tt < (unsigned)sl.T))};
         };
         auto word = [&](Line ln, int cx) -> uint2 {
@@ -1119,53 +1130,67 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         }
       }
     } else {
-      // ---- the brick's count box: one global->LDS copy per box row from the
-      //      pair grid (lanes outside the slice read zeros); it has landed once
-      //      the first chunk's prologue wait returns
+      // ---- the brick's count box, as overlapping fp16 pairs, from the counts
       const SliceDesc sl =
           uniform(a.bt.nslices == 1 ? a.bt.s0 : a.lds_slices ? stab[si] : a.bt.table[si]);
       const int lb = bid - sl.brick_off;
       const int bxi = lb % sl.nbx, byi = (lb / sl.nbx) % sl.nby, bti = lb / (sl.nbx * sl.nby);
-      const int xb = bxi * a.b.bx - a.rx - kRunPad, x = xb + lane;
+      const int x = bxi * a.b.bx - a.rx - kRunPad + lane;
       const int y0 = byi * a.b.by - a.ry, tb = bti * a.b.bt - a.rt;
-      const bool col = lane < a.SX;
-      const bool xin = col && x >= -1 && x < sl.W;  // the pair grid has a column for x = -1
       const int nrows = a.SY * a.ST;
-      // (the row's address is the same for all lanes: scalar registers)
-      const uint32_t* box = a.pairs + sl.pair_off + (xb + 1);
-      const uint32_t vbox = lds_offset(vol2);
-      if (xb >= -1 && xb + a.SX <= sl.W && a.SX % 4 == 0) {
-        // every column in the slice: 4 voxels per lane, 64 lanes per copy over
-        // the rows' boundaries (the box is consecutive in LDS)
-        const int quads = a.SX / 4, total = nrows * quads;
-        const uint32_t plane = (uint32_t)(sl.W + 1) * sl.H;
-        for (int q0 = wid * 64; q0 < total; q0 += NW * 64) {
-          const int q = q0 + lane, rr = q / quads, c = q - rr * quads;
-          const int st = rr / a.SY, y = y0 + rr - st * a.SY, t = tb + st;
-          const bool in = ((unsigned)y < (unsigned)sl.H) & ((unsigned)t < (unsigned)sl.T);
+      // 16 lanes take a box row, 4 voxels each (the right neighbour's count is the
+      // next lane's; the last column's is never read): a wave loads 4 rows at
+      // once and a batch of them before any is used (12 instead of 6 spill).
+      // Voxels outside the slice are masked; reads of up to kGridPad voxels
+      // around the grid stay inside its allocation.  A row per wave and a voxel
+      // per lane took 13.6k cycles for the 364 rows at r = 5/3, mostly issue
+      // (1M-event slice, FP16 form, whole call 0.373 against 0.356 ms).
+      const int l16 = lane & 15, xq = x + 3 * l16 - 16 * (lane >> 4);  // 4 l16 from the first column
+      const int w4 = (a.SX + 3) >> 2;
+      const bool whole = (a.SX & 3) == 0;
+      const uint32_t inv = ((1u << 20) + a.SY - 1) / a.SY;  // rr / SY = rr inv >> 20 (rr < 2048)
+      typedef int intx4u __attribute__((ext_vector_type(4), aligned(4)));
+      const int32_t* cnt = a.count + sl.grid_off;
+      constexpr int kR = 6;
+      for (int r0 = wid * 4 + (lane >> 4); r0 - (lane >> 4) < nrows; r0 += NW * 4 * kR) {
+        intx4u v[kR];
+        uint32_t rows_in = 0;
+#pragma unroll
+        for (int u = 0; u < kR; ++u) {
+          const int rr = r0 + u * NW * 4;
+          const int st = (int)((uint32_t)rr * inv >> 20), y = y0 + rr - st * a.SY, t = tb + st;
+          const bool in = (rr < nrows) & ((unsigned)y < (unsigned)sl.H) & ((unsigned)t < (unsigned)sl.T);
           const int tp = t + sl.tshift < sl.T ? t + sl.tshift : t + sl.tshift - sl.T;  // ring plane
-          const uint32_t* src =
-              in ? box + ((int64_t)tp * plane + (uint32_t)(y * (sl.W + 1) + 4 * c)) : a.zeros;
-          if (q < total) copy_to_lds16(src, vbox + q0 * 16);
+          rows_in |= in ? 1u << u : 0u;
+          v[u] = *reinterpret_cast<const intx4u*>(cnt + (in ? (tp * sl.H + y) * sl.W + xq : 0));
         }
-      } else {
-      int sy = wid % a.SY, st = wid / a.SY;
-      for (int rr = wid; rr < nrows; rr += NW) {
-        const int y = y0 + sy, t = tb + st;
-        const bool in = (unsigned)y < (unsigned)sl.H && (unsigned)t < (unsigned)sl.T;
-        if (in) {
-          const int tp = t + sl.tshift < sl.T ? t + sl.tshift : t + sl.tshift - sl.T;  // ring plane
-          // (before the row's start for lanes of the first columns, which are masked)
-          const uint32_t* src = box + ((int64_t)tp * sl.H + y) * (sl.W + 1);
-          if (xin) copy_to_lds4_s(src, (uint32_t)lane * 4, vbox + rr * a.SX * 4);
+#pragma unroll
+        for (int u = 0; u < kR; ++u) {
+          const int rr = r0 + u * NW * 4;
+          const bool in = (rows_in >> u) & 1;
+          float f[5];
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            f[k] = in && (unsigned)(xq + k) < (unsigned)sl.W ? (float)v[u][k] : 0.f;
+          f[4] = __int_as_float(
+              __builtin_amdgcn_update_dpp(0, __float_as_int(f[0]), 0x101, 0xf, 0xf, true));  // lane + 1
+          uint32_t w[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const auto h = __builtin_amdgcn_cvt_pkrtz(f[k], f[k + 1]);  // (exact: at most 1024)
+            __builtin_memcpy(&w[k], &h, 4);
+          }
+          if (rr < nrows && l16 < w4) {
+            uint32_t* to = vol2 + rr * a.SX + 4 * l16;
+            if (whole) {
+              *reinterpret_cast<uint4*>(to) = make_uint4(w[0], w[1], w[2], w[3]);
+            } else {  // (rows end within a lane's four)
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+                if (4 * l16 + k < a.SX) to[k] = w[k];
+            }
+          }
         }
-        if (col && !(in && xin)) vol2[rr * a.SX + lane] = 0;
-        sy += NW;
-        while (sy >= a.SY) {
-          sy -= a.SY;
-          ++st;
-        }
-      }
       }
     }
 
@@ -1216,6 +1241,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
       if (single) {
         const int r = wm * 16 + (lane & 15);
         const int rstride = single_row_dwords(a.nsteps);
+        rr.planes = a.bt.nslices == 1 && a.bt.s0.tshift != 0 ? a.bt.s0.T : 2 * kNoRing;
         rr.lut = (const lds_uint2*)vol2;
         rr.head = (const lds_uint4*)(heads + r);
         rr.hstride = WM * 16;

@@ -112,8 +112,8 @@ int launch_encode(const Batch& bt, const Workspace& w, const EncodeTables& et, i
   a.frag = reinterpret_cast<const uint4*>(et.frag);
   a.runs = et.runs;
   a.wts = et.wts;
+  a.count = w.count;
   a.pairs = w.pairs;
-  a.zeros = w.zeros;
   a.rows = w.rows;
   a.plan = w.plan;
   if (a.SX > 64) return VECKM_E_INVAL;  // one wavefront copies one box row

@@ -64,9 +64,8 @@ __device__ inline SliceDesc slice_by_event_block(const Batch& bt, int i) {
 // calls) the event also flags its brick x row: lines[gb * by * bt + lt * by +
 // ly] = 1 for brick gb and brick-local row (ly, lt), so that ranking visits
 // only rows that hold events (plain byte stores: every writer stores the
-// same value).  Voxels over VECKM_MAX_VOXEL_EVENTS are caught where the pair
-// grid is built (k_rank_lines, k_rank, or k_pairs for a sliding window),
-// which reads every count once.
+// same value).  Voxels over VECKM_MAX_VOXEL_EVENTS are caught where every
+// count is read once (k_rank_lines, or k_bits for a sliding window).
 template <bool ADD>
 __global__ void k_scatter(const int4* __restrict__ ev, Batch bt, int32_t* __restrict__ count,
                           int32_t* __restrict__ vox, int32_t* __restrict__ err,
@@ -113,50 +112,52 @@ __global__ void k_push(const int4* __restrict__ ev, int n, int W, int H, int T, 
   atomicAdd(&count[((int64_t)plane * H + e.y) * W + e.x], 1);
 }
 
-// The encoder's view of the counts: per slice, rows of W + 1 dwords; entry
-// x + 1 of a row holds the fp16 counts of voxels x and x + 1 of that x row
-// (0 outside [0, W)), for x in [-1, W).  Any 4 consecutive voxels of a row
-// then sit in two aligned dwords, including a run that starts at x = -1.
-// Exact: counts are at most VECKM_MAX_VOXEL_EVENTS.
-// The pair grid of a sliding window's new planes (slice calls build it in
-// k_rank).  One wavefront per x row; blockIdx.y picks the slice, the blocks
-// of a slice stride over its H T rows.
-__global__ __launch_bounds__(256) void k_pairs(Batch bt, const int32_t* __restrict__ count,
-                                               uint32_t* __restrict__ pairs,
-                                               int32_t* __restrict__ err) {
-  const SliceDesc s = bt.nslices > 1 ? bt.table[blockIdx.y] : bt.s0;
+// The two pair-grid entries that hold a voxel of 3 or more events (`c`: its
+// count, `hi` of them): per slice, rows of W + 1 dwords; entry x + 1 of a row
+// holds the fp16 counts of voxels x and x + 1 of that x row (0 outside [0, W)),
+// for x in [-1, W).  Only these entries are written, and only they are read:
+// a single row takes smaller counts from the bits, a brick's box all counts
+// from the count grid.  (Two such voxels side by side write the same entry
+// with the same value.)  Exact: counts are at most VECKM_MAX_VOXEL_EVENTS.
+__device__ inline void put_pairs(const int32_t* c, int x, int W, int hi, uint32_t* row) {
+  const int left = x > 0 ? c[-1] : 0, right = x + 1 < W ? c[1] : 0;
+  const uint32_t h = __half_as_ushort(__float2half((float)hi));
+  row[x] = (uint32_t)__half_as_ushort(__float2half((float)left)) | h << 16;
+  row[x + 1] = h | (uint32_t)__half_as_ushort(__float2half((float)right)) << 16;
+}
+
+// The bits (brick_bits) of a step's x rows, one store per row: bx consecutive
+// lanes each, a lane's voxel has `count` events.
+__device__ inline void put_bits(int count, bool valid, uint2* at, int lane, int bx) {
+  const unsigned long long bo = __ballot(count == 1 || count > 2), bm = __ballot(count > 1);
+  if (valid && (lane & (bx - 1)) == 0) {
+    const uint32_t mask = bx >= 32 ? ~0u : (1u << bx) - 1u;
+    *at = make_uint2((uint32_t)(bo >> lane) & mask, (uint32_t)(bm >> lane) & mask);
+  }
+}
+
+// A sliding window's planes [p0, p0 + np) of the ring (slice calls do this
+// while ranking): the bits of their brick x rows (bins counted as planes), the
+// pair entries of voxels of 3 or more events, and the check of the counts.  A
+// wave per 64 voxels of an x row, strided over the planes' rows.
+__global__ __launch_bounds__(256) void k_bits(SliceDesc s, Brick b, int p0, int np,
+                                              const int32_t* __restrict__ count,
+                                              uint32_t* __restrict__ pairs,
+                                              uint2* __restrict__ bits, int32_t* __restrict__ err) {
   const int lane = threadIdx.x & 63;
-  const int W = s.W, nrows = s.H * s.T;
+  const int sx = __builtin_ctz(b.bx), sy = __builtin_ctz(b.by), st = __builtin_ctz(b.bt);
+  const int per_row = (s.W + 63) >> 6, total = np * s.H * per_row;
   bool bad = false;
-  for (int row = blockIdx.x * 4 + (threadIdx.x >> 6); row < nrows; row += gridDim.x * 4) {
-    const int32_t* c = count + s.grid_off + (int64_t)row * W;
-    uint32_t* p = pairs + s.pair_off + (int64_t)row * (W + 1);
-    for (int e0 = 0; e0 <= W; e0 += 256) {
-      // entries e0 + 64 u + lane (entry e: voxels e - 1 and e).  The loads
-      // are unconditional (addresses clamped into the row, values masked
-      // afterwards), so all eight are in flight before the first wait.
-      int lo[4], hi[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + 64 * u + lane;
-        lo[u] = c[min(max(e - 1, 0), W - 1)];
-        hi[u] = c[min(e, W - 1)];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + 64 * u + lane;
-        lo[u] = e >= 1 && e <= W ? lo[u] : 0;
-        hi[u] = e < W ? hi[u] : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + 64 * u + lane;
-        bad |= hi[u] > VECKM_MAX_VOXEL_EVENTS;
-        if (e <= W)
-          p[e] = (uint32_t)__half_as_ushort(__float2half((float)lo[u])) |
-                 ((uint32_t)__half_as_ushort(__float2half((float)hi[u])) << 16);
-      }
-    }
+  for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < total; i += gridDim.x * 4) {
+    const int x = (i % per_row) * 64 + lane, r = i / per_row;
+    const int y = r % s.H, p = p0 + r / s.H;
+    const int32_t* c = count + ((int64_t)p * s.H + y) * s.W + x;
+    const int hi = x < s.W ? *c : 0;
+    bad |= hi > VECKM_MAX_VOXEL_EVENTS;
+    if (hi > 2) put_pairs(c, x, s.W, hi, pairs + ((int64_t)p * s.H + y) * (s.W + 1));
+    const int64_t brick = ((int64_t)(p >> st) * s.nby + (y >> sy)) * s.nbx + (x >> sx);
+    put_bits(hi, x < s.W,
+             bits + brick * (b.by * b.bt) + (((p & (b.bt - 1)) << sy) | (y & (b.by - 1))), lane, b.bx);
   }
   if (bad) atomicOr(err, kErrOverflow);
 }
@@ -272,17 +273,6 @@ __global__ __launch_bounds__(256) void k_rank(Batch bt, Brick b, const int32_t* 
 //
 // Both kernels write the bits of every brick x row (flagged or not): the
 // encoder collects a single row's window from them.
-//
-// The words of a step's x rows (bx consecutive lanes each, a lane's voxel has
-// `count` events), one store per row.
-__device__ inline void put_bits(int count, bool valid, uint2* at, int lane, int bx) {
-  const unsigned long long bo = __ballot(count == 1 || count > 2), bm = __ballot(count > 1);
-  if (valid && (lane & (bx - 1)) == 0) {
-    const uint32_t mask = bx >= 32 ? ~0u : (1u << bx) - 1u;
-    *at = make_uint2((uint32_t)(bo >> lane) & mask, (uint32_t)(bm >> lane) & mask);
-  }
-}
-
 template <bool ALL>
 __global__ __launch_bounds__(256) void k_rank_lines(Batch bt, Brick b,
                                                     const int32_t* __restrict__ count,
@@ -350,7 +340,6 @@ __global__ __launch_bounds__(256) void k_rank_lines(Batch bt, Brick b,
     return (t * s.H + y) * s.W + x;
   };
   const int32_t* cnt = count + s.grid_off;
-  const bool has_left = lx == 0 && x > 0, has_right = lx == b.bx - 1 && x + 1 < s.W;
   const int steps = (nr + rps - 1) / rps;
   int base = 0;
   bool bad = false;
@@ -363,32 +352,23 @@ __global__ __launch_bounds__(256) void k_rank_lines(Batch bt, Brick b,
       lf[g] = j < nr && x < s.W;
       lis[g] = j < nr ? ((int)rows[j] << sx) + lx : 0;
     }
-    int cv[kG], side[kG];
+    int cv[kG];
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
-      const int o = at(lis[g]);
-      cv[g] = lf[g] ? cnt[o] : 0;
-      side[g] = lf[g] && (has_left || has_right) ? cnt[has_left ? o - 1 : o + 1] : 0;
+      cv[g] = lf[g] ? cnt[at(lis[g])] : 0;
     }
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
       if (k0 + g >= steps) break;  // (wave-uniform)
-      const int up = __shfl_up(cv[g], 1);  // (all lanes)
       const int li = lis[g];
       bool f = false;
       if (lf[g]) {
         const int y = y0 + ((li >> sx) & (b.by - 1)), t = t0 + (li >> (sx + sy));
-        const int lo = lx > 0 ? up : side[g];
         const int hi = cv[g];
         bad |= hi > VECKM_MAX_VOXEL_EVENTS;
-        uint32_t* row = pairs + s.pair_off + ((int64_t)t * s.H + y) * (s.W + 1);
-        row[x] = (uint32_t)__half_as_ushort(__float2half((float)lo)) |
-                 ((uint32_t)__half_as_ushort(__float2half((float)hi)) << 16);
-        if (lx == b.bx - 1 || x == s.W - 1) {
-          const int right = x + 1 < s.W ? side[g] : 0;
-          row[x + 1] = (uint32_t)__half_as_ushort(__float2half((float)hi)) |
-                       ((uint32_t)__half_as_ushort(__float2half((float)right)) << 16);
-        }
+        if (hi > 2)
+          put_pairs(cnt + at(li), x, s.W, hi,
+                    pairs + s.pair_off + ((int64_t)t * s.H + y) * (s.W + 1));
         f = ALL ? hi > 0 : qmark[s.grid_off + at(li)] != 0;
       }
       put_bits(cv[g], (k0 + g) * rps + slot < nr,
@@ -461,7 +441,6 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
     return (t * s.H + y) * s.W + x;
   };
   const int32_t* cnt = count + s.grid_off;
-  const bool has_left = lx == 0 && x > 0, has_right = lx == b.bx - 1 && x + 1 < s.W;
   const int steps = (BV + 63) >> 6;
   const int per = (steps + NW - 1) / NW;  // steps of each wave
   const int k_lo = wid * per, k_hi = min(k_lo + per, steps);
@@ -486,31 +465,22 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
       }
       continue;
     }
-    int cv[kG], side[kG];
+    int cv[kG];
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
-      const int o = at((k0 + g) * 64 + lane);
-      cv[g] = lf[g] ? cnt[o] : 0;
-      side[g] = lf[g] && (has_left || has_right) ? cnt[has_left ? o - 1 : o + 1] : 0;
+      cv[g] = lf[g] ? cnt[at((k0 + g) * 64 + lane)] : 0;
     }
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
-      const int up = __shfl_up(cv[g], 1);  // (all lanes)
       const int li = (k0 + g) * 64 + lane;
       bool f = false;
       if (lf[g]) {
         const int y = y0 + ((li >> sx) & (b.by - 1)), t = t0 + (li >> (sx + sy));
-        const int lo = lx > 0 ? up : side[g];
         const int hi = cv[g];
         bad |= hi > VECKM_MAX_VOXEL_EVENTS;
-        uint32_t* row = pairs + s.pair_off + ((int64_t)t * s.H + y) * (s.W + 1);
-        row[x] = (uint32_t)__half_as_ushort(__float2half((float)lo)) |
-                 ((uint32_t)__half_as_ushort(__float2half((float)hi)) << 16);
-        if (lx == b.bx - 1 || x == s.W - 1) {
-          const int right = x + 1 < s.W ? side[g] : 0;
-          row[x + 1] = (uint32_t)__half_as_ushort(__float2half((float)hi)) |
-                       ((uint32_t)__half_as_ushort(__float2half((float)right)) << 16);
-        }
+        if (hi > 2)
+          put_pairs(cnt + at(li), x, s.W, hi,
+                    pairs + s.pair_off + ((int64_t)t * s.H + y) * (s.W + 1));
         f = ALL ? hi > 0 : qmark[s.grid_off + at(li)] != 0;
       }
       put_bits(cv[g], k0 + g < k_hi && li < BV,
@@ -545,40 +515,24 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
   }
 }
 
-// The count and pair grids of a dense call back to zero: one pass over both
-// (cheaper than the per-event stores when the grids are small beside the
-// events; see dense_batch).
-__device__ inline void fill2_zero(int blk, int nblk, int32_t* __restrict__ a, int64_t na,
-                                  uint32_t* __restrict__ b, int64_t nb) {
+// The count grid of a dense call back to zero in one pass (cheaper than the
+// per-event stores when the grid is small beside the events; see dense_batch).
+__device__ inline void fill_zero(int blk, int nblk, int32_t* __restrict__ a, int64_t n) {
   const int64_t stride = (int64_t)nblk * blockDim.x;
-  for (int64_t i = (int64_t)blk * blockDim.x + threadIdx.x; i < na + nb; i += stride) {
-    if (i < na) a[i] = 0;
-    else b[i - na] = 0u;
-  }
+  for (int64_t i = (int64_t)blk * blockDim.x + threadIdx.x; i < n; i += stride) a[i] = 0;
 }
 
-__global__ void k_fill2_zero(int32_t* __restrict__ a, int64_t na, uint32_t* __restrict__ b,
-                             int64_t nb) {
-  fill2_zero(blockIdx.x, gridDim.x, a, na, b, nb);
-}
-
-// After a bounded-window slice call: every valid event's voxel count and
-// the two pair entries that hold it (entries x and x + 1 of its row) back to
-// zero; events that share a voxel store the same zeros.  These are all the
-// non-zero entries (an entry holds the counts of voxels x - 1 and x).  The
-// row flags were cleared by the ranking kernel, their last reader.
+// After a bounded-window slice call: every valid event's voxel count back to
+// zero; events that share a voxel store the same zero.  The row flags were
+// cleared by the ranking kernel, their last reader.
 __global__ void k_clear_events(Batch bt, const int32_t* __restrict__ vox,
-                               int32_t* __restrict__ count, uint32_t* __restrict__ pairs) {
+                               int32_t* __restrict__ count) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (blockIdx.x * blockDim.x >= bt.n) return;  // (whole block; launches never do this)
   const SliceDesc s = slice_by_event_block(bt, i);
   if (i >= bt.n) return;
   const int v = vox[i];
-  if (v < 0) return;
-  count[s.grid_off + v] = 0;
-  const int64_t e = s.pair_off + v + v / s.W;  // entry x of row v / W
-  pairs[e] = 0u;
-  pairs[e + 1] = 0u;
+  if (v >= 0) count[s.grid_off + v] = 0;
 }
 
 // Exclusive scan of the per-brick row counts into off[] (off[nb] = total
@@ -1021,9 +975,9 @@ __global__ void k_expand_flow_q(const int32_t* __restrict__ queries, Batch bt, B
   expand_flow_q<SUB>(blockIdx.x, queries, bt, b, vox, rank, brick_off, rowflow, out);
 }
 
-// The flows of a dense call and the clear of its count and pair grids in one
-// launch: blocks [0, eb) expand, the others zero the grids (k_fill2_zero's
-// work).  The expansion reads neither grid, so the two parts need no order,
+// The flows of a dense call and the clear of its count grid in one
+// launch: blocks [0, eb) expand, the others zero the grid.  The
+// expansion does not read it, so the two parts need no order,
 // and the call saves a launch.
 template <bool SUB>
 __global__ void k_expand_flow_q_fill(const int32_t* __restrict__ queries, Batch bt, Brick b,
@@ -1031,12 +985,11 @@ __global__ void k_expand_flow_q_fill(const int32_t* __restrict__ queries, Batch 
                                      const int32_t* __restrict__ rank,
                                      const int32_t* __restrict__ brick_off,
                                      const float2* __restrict__ rowflow, float2* __restrict__ out,
-                                     int eb, int32_t* __restrict__ count,
-                                     uint32_t* __restrict__ pairs) {
+                                     int eb, int32_t* __restrict__ count) {
   if ((int)blockIdx.x < eb)
     expand_flow_q<SUB>(blockIdx.x, queries, bt, b, vox, rank, brick_off, rowflow, out);
   else
-    fill2_zero(blockIdx.x - eb, gridDim.x - eb, count, bt.nvox, pairs, bt.npairs);
+    fill_zero(blockIdx.x - eb, gridDim.x - eb, count, bt.nvox);
 }
 
 template <bool SUB>
@@ -1076,17 +1029,7 @@ static int fill_grid(int64_t n) {
   return (int)(b < 8192 ? (b < 1 ? 1 : b) : 8192);
 }
 
-// k_pairs over nslices slices of at most max_rows x rows each: about 4096
-// blocks in all (4 rows at a time per block).
-static dim3 pairs_grid(int nslices, int64_t max_rows) {
-  int64_t x = (4096 + nslices - 1) / nslices;
-  const int64_t need = (max_rows + 3) / 4;
-  x = x < need ? x : need;
-  return dim3((unsigned)(x < 1 ? 1 : x), (unsigned)nslices);
-}
-
-// k_rank for every voxel with events (all) or only the marked ones; with
-// `pairs` it also builds the pair grid.
+// k_rank for every voxel with events (all) or only the marked ones.
 static void launch_rank(const Batch& bt, const Workspace& w, const Brick& b, bool all,
                         hipStream_t s) {
   static_assert(kMaxBrickVoxels <= 8192, "k_rank holds at most 32 ballots per wave");
@@ -1140,19 +1083,17 @@ static void launch_rank_lines(const Batch& bt, const Workspace& w, const Brick& 
 
 int launch_clear_events(const Batch& bt, const Workspace& w, void* stream) {
   if (dense_batch(bt))
-    hipLaunchKernelGGL(k_fill2_zero, dim3(fill_grid(bt.nvox + bt.npairs)), dim3(256), 0,
-                       (hipStream_t)stream, w.count, bt.nvox, w.pairs, bt.npairs);
+    hipLaunchKernelGGL(k_fill_i32, dim3(fill_grid(bt.nvox)), dim3(256), 0, (hipStream_t)stream,
+                       w.count, bt.nvox, 0);
   else if (bt.n > 0)
     hipLaunchKernelGGL(k_clear_events, dim3(blocks_for(bt.n, 256)), dim3(256), 0,
-                       (hipStream_t)stream, bt, w.vox, w.count, w.pairs);
+                       (hipStream_t)stream, bt, w.vox, w.count);
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
 
 int launch_clear_grids(const Batch& bt, const Workspace& w, int64_t nlines, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(k_fill_i32, dim3(fill_grid(bt.nvox)), dim3(256), 0, s, w.count, bt.nvox, 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3(fill_grid(bt.npairs)), dim3(256), 0, s,
-                     reinterpret_cast<int32_t*>(w.pairs), bt.npairs, 0);
   const int64_t words = (nlines + 3) / 4;
   hipLaunchKernelGGL(k_fill_i32, dim3(fill_grid(words)), dim3(256), 0, s,
                      reinterpret_cast<int32_t*>(w.lines), words, 0);
@@ -1193,12 +1134,23 @@ int launch_prepare(const Batch& bt, const Workspace& w, const veckm_event* ev,
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
 
-int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, int W, int H, int T,
-                       int t0, int nbins, int tref, int64_t clear_b0, int clear_nb, void* stream) {
+int launch_window_bits(const Workspace& w, const Batch& bt, const Brick& b, int p0, int np,
+                       void* stream) {
+  const int64_t waves = (int64_t)np * bt.s0.H * ((bt.s0.W + 63) / 64);
+  const int64_t blocks = std::min<int64_t>(8192, (waves + 3) / 4);
+  hipLaunchKernelGGL(k_bits, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, bt.s0, b, p0,
+                     np, w.count, w.pairs, reinterpret_cast<uint2*>(brick_bits(w)), w.err);
+  return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
+}
+
+int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, const Batch& bt,
+                       const Brick& b, int t0, int nbins, int tref, int64_t clear_b0, int clear_nb,
+                       void* stream) {
+  const int W = bt.s0.W, H = bt.s0.H, T = bt.s0.T;
   hipStream_t s = (hipStream_t)stream;
-  const int64_t plane = (int64_t)W * H, pplane = (int64_t)(W + 1) * H;
+  const int64_t plane = (int64_t)W * H;
   // the planes of the bins that enter the window: clear them, count the new
-  // events, rebuild their pairs
+  // events, rebuild their bits
   const int p0 = (int)((clear_b0 - tref) % T);
   const int first = clear_nb < T - p0 ? clear_nb : T - p0;  // planes before the ring wraps
   const int span[2][2] = {{p0, first}, {0, clear_nb - first}};
@@ -1212,14 +1164,8 @@ int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, int
                        w.count, w.err);
   for (const auto& sp : span)
     if (sp[1] > 0) {
-      Batch pb{};
-      pb.s0.W = W;
-      pb.s0.H = H;
-      pb.s0.T = sp[1];
-      pb.nslices = 1;
-      pb.npairs = sp[1] * pplane;
-      hipLaunchKernelGGL(k_pairs, pairs_grid(1, (int64_t)H * sp[1]), dim3(256), 0, s, pb,
-                         w.count + sp[0] * plane, w.pairs + sp[0] * pplane, w.err);
+      const int rc = launch_window_bits(w, bt, b, sp[0], sp[1], stream);
+      if (rc) return rc;
     }
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
@@ -1234,7 +1180,8 @@ int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event
                        et.brick, (uint8_t*)nullptr);
   }
   launch_rank(bt, w, et.brick, false, s);
-  launch_work_list(bt, w, et, num_cus, false, s);  // (a window's rows have no bits: bricks only)
+  // (a plane number has 15 bits in a single row's record)
+  launch_work_list(bt, w, et, num_cus, bt.s0.T < 1 << 15, s);
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
 
@@ -1285,16 +1232,16 @@ int launch_expand_flow_clear(const Batch& bt, const Workspace& w, const int32_t*
                              const Brick& b, float* flow, void* stream) {
   if (!dense_batch(bt)) return VECKM_E_INVAL;
   const int eb = bt.m > 0 ? blocks_for(bt.m, 256) : 0;
-  const dim3 grid(eb + fill_grid(bt.nvox + bt.npairs));
+  const dim3 grid(eb + fill_grid(bt.nvox));
   const float2* rf = reinterpret_cast<const float2*>(w.rowflow);
   float2* out = reinterpret_cast<float2*>(flow);
   hipStream_t s = (hipStream_t)stream;
   if (queries)
     hipLaunchKernelGGL(k_expand_flow_q_fill<true>, grid, dim3(256), 0, s, queries, bt, b, w.vox,
-                       w.rank, w.brick_off, rf, out, eb, w.count, w.pairs);
+                       w.rank, w.brick_off, rf, out, eb, w.count);
   else
     hipLaunchKernelGGL(k_expand_flow_q_fill<false>, grid, dim3(256), 0, s, queries, bt, b, w.vox,
-                       w.rank, w.brick_off, rf, out, eb, w.count, w.pairs);
+                       w.rank, w.brick_off, rf, out, eb, w.count);
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
 

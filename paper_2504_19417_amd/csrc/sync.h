@@ -29,8 +29,8 @@ __device__ inline uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(lds_cptr)(p);
 }
 
-// gfx950 global->LDS copies: lane i's 16 (4) bytes at `src` go to LDS byte
-// lds_base + 16 i (4 i); lds_base must be wave-uniform.  The leading s_nop 4
+// gfx950 global->LDS copies: lane i's 16 bytes at `src` go to LDS byte
+// lds_base + 16 i; lds_base must be wave-uniform.  The leading s_nop 4
 // gives the five wait states the hardware needs between a vector-ALU write of
 // a scalar register (an SGPR spill reload by v_readlane, a v_readfirstlane
 // into M0) and a vector memory instruction that reads it (the M0 base, the
@@ -44,15 +44,6 @@ __device__ inline void copy_to_lds16(const void* src, uint32_t lds_base) {
 // lane's 32-bit byte offset: no 64-bit address per copy in vector registers.
 __device__ inline void copy_to_lds16_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(voff), "s"(sbase), "{m0}"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
-}
-__device__ inline void copy_to_lds4(const void* src, uint32_t lds_base) {
-  asm volatile("s_nop 4\n\tglobal_load_lds_dword %0, off"
-               :: "v"(src), "{m0}"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
-}
-// (masked-off lanes copy nothing; the others' places do not move)
-__device__ inline void copy_to_lds4_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_nop 4\n\tglobal_load_lds_dword %0, %1"
                :: "v"(voff), "s"(sbase), "{m0}"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
 }
 

@@ -93,6 +93,9 @@ int lds_volume_halves(const Brick& b, int rx, int ry, int rt);
 // layout ever leaves a box row.
 constexpr int kRunPad = 3;
 inline int box_sx(const Brick& b, int rx) { return b.bx + 2 * rx + 2 * kRunPad; }
+// Voxels around the count grid that the encoder may read (and ignores): a box
+// row sticks out of the slice by less.
+constexpr int kGridPad = 64;
 inline int box_dwords(const Brick& b, int rx, int ry, int rt) {
   return box_sx(b, rx) * (b.by + 2 * ry) * (b.bt + 2 * rt);
 }
@@ -140,11 +143,11 @@ struct Workspace {
                                 // voxels to zero after each call; the paper form fills it
                                 // before its scatter)
   uint32_t* pairs = nullptr;    // (W + 1) H T per slice: entry x + 1 of a row holds the fp16
-                                // counts of voxels x and x + 1 of that row, x in [-1, W); all
-                                // zero between bounded-window slice calls, like count
+                                // counts of voxels x and x + 1 of that row, x in [-1, W); only
+                                // the entries of voxels with 3 or more events are written (and
+                                // read) by a call
   uint8_t* lines = nullptr;     // bricks x (by bt): 1 where the brick's x row holds an event;
                                 // all zero between slice calls (the ranking kernel clears them)
-  const uint32_t* zeros = nullptr;  // 64 zero dwords (out-of-grid reads)
   int32_t* rank = nullptr;      // voxels: brick-local rank of query voxels
   uint8_t* qmark = nullptr;     // voxels: query-voxel marks (query subsets, windows); all zero
                                 // between calls (the ranking pass clears the marks it reads)
@@ -282,7 +285,7 @@ bool mlp_rows_split(int d, int hidden);
 int launch_expand_flow(const Batch& bt, const Workspace& w, const int32_t* queries,
                        const Brick& b, bool use_qmap, float* flow, void* stream);
 // The flows of a dense bounded-window slice call (dense_batch) and the clear
-// of its count and pair grids, in one launch (launch_expand_flow followed by
+// of its count grid, in one launch (launch_expand_flow followed by
 // launch_clear_events); VECKM_E_INVAL for a call that is not dense.
 int launch_expand_flow_clear(const Batch& bt, const Workspace& w, const int32_t* queries,
                              const Brick& b, float* flow, void* stream);
@@ -290,17 +293,16 @@ int launch_expand_flow_clear(const Batch& bt, const Workspace& w, const int32_t*
 // w.rowflow); -1 for an invalid query.
 int launch_expand_count(const Batch& bt, const Workspace& w, const int32_t* queries,
                         const Brick& b, int32_t* counts, void* stream);
-// Whether a bounded-window slice call is dense: its count and pair grids
-// hold fewer than 30 entries per event.  Dense calls clear the two grids
-// with one pass over them (about 1.5 GB/ms against about 50 M events/ms for
-// per-event stores) and rank a brick per block.
+// Whether a bounded-window slice call is dense: its grids hold fewer than 30
+// entries per event.  Dense calls clear the count grid with one pass over it
+// (per-event stores take longer) and rank a brick per block.
 inline bool dense_batch(const Batch& bt) { return bt.nvox + bt.npairs < 30 * (int64_t)bt.n; }
 // After a bounded-window slice call whose launches all went through: the
-// counts and pair entries of its events' voxels back to zero (the ranking
-// kernel has cleared the row flags).
+// counts of its events' voxels back to zero (the ranking kernel has cleared
+// the row flags).
 int launch_clear_events(const Batch& bt, const Workspace& w, void* stream);
-// Dense fill of the count grid, the pair grid and `nlines` row flags (for
-// workspaces whose contents are unknown).
+// Dense fill of the count grid and `nlines` row flags (for workspaces whose
+// contents are unknown).
 int launch_clear_grids(const Batch& bt, const Workspace& w, int64_t nlines, void* stream);
 // Copies the device error bits to `host` (pinned) and clears them, in stream order.
 int launch_take_err(const Workspace& w, int32_t* host, void* stream);
@@ -308,8 +310,12 @@ int launch_take_err(const Workspace& w, int32_t* host, void* stream);
 // T planes (bin b in plane (b - tref) mod T, clear_nb <= T); the events of
 // bins [t0, t0 + nbins) among them are counted.  Then an encode of query
 // events against the resident window (bt describes the window, tshift set).
-int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, int W, int H, int T,
-                       int t0, int nbins, int tref, int64_t clear_b0, int clear_nb, void* stream);
+int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, const Batch& bt,
+                       const Brick& b, int t0, int nbins, int tref, int64_t clear_b0, int clear_nb,
+                       void* stream);
+// Rebuilds what ranking keeps per brick x row of ring planes [p0, p0 + np).
+int launch_window_bits(const Workspace& w, const Batch& bt, const Brick& b, int p0, int np,
+                       void* stream);
 int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event* queries,
                           const EncodeTables& et, int num_cus, void* stream);
 

@@ -88,3 +88,31 @@ def test_batch_rows_match_single_calls(vk):
         off += n
         one.close()
     c.close()
+
+
+def test_window_rows_match_a_slice(vk):
+    """A sliding window (ring planes wrap, voxels of 3 and more events in wrapped
+    planes, the tiling changed mid-stream) gives the rows of a slice that holds
+    the window's events, bit for bit."""
+    W, H, T, rx, ry, rt, d, n = 75, 40, 7, 5, 4, 3, 128, 900
+    A = synth.draw_frequencies(d, rx, ry, rt)
+    win = vk.Window(W, H, rx, ry, rt, A, T, n, "fp32")
+    one = vk.Context(W, H, rx, ry, rt, A, T, T * n, "fp32")
+    bins = []
+    for k in range(2 * T + 3):
+        ev, _ = _events(8300 + k, W, H, 1, n, t0=100 + k)
+        bins.append(ev)
+        win.push(torch.from_numpy(ev).cuda(), 100 + k, 1)
+        if k == T + 2:
+            win.select_tiling(len(win.tilings()) - 1)
+        if k < T:
+            continue
+        q = torch.from_numpy(bins[k - rt]).cuda()
+        got = win.encode_window(q).cpu().numpy()
+        held = np.concatenate(bins[k - T + 1:k + 1])
+        m = sum(len(b) for b in bins[k - T + 1:k - rt])
+        one.select_tiling(win.tiling())
+        ref = one.encode(torch.from_numpy(held).cuda(), 100 + k - T + 1, T).cpu().numpy()
+        assert np.array_equal(got, ref[m:m + n])
+    win.close()
+    one.close()
