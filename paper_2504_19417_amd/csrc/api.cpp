@@ -394,8 +394,8 @@ int run(veckm_ctx* c, const Workspace& w, const Batch& bt, const veckm_event* ev
   {
     StageTimer t(c, VECKM_STAGE_ENCODE, stream);
     // the encoder writes fp32 rows unless the perceptron takes bf16 or hi/lo
-    // rows, or runs inside the encoder
-    const int erows = rows == kRowsBF16 || rows == kRowsHiLo16 || fused ? rows : kRowsF32;
+    // rows, forms the rows itself (paper form) or runs inside the encoder
+    const int erows = rows == kRowsBF16 || rows == kRowsHiLo16 || rows == kRowsSplit16 || fused ? rows : kRowsF32;
     const int rc = c->paper ? launch_paper_encode(bt, w, c->pt, c->et.brick, erows, c->num_cus, stream)
                             : launch_encode(bt, w, c->et, erows, c->num_cus, stream,
                                             counts ? reinterpret_cast<int32_t*>(w.rowflow)
@@ -408,7 +408,8 @@ int run(veckm_ctx* c, const Workspace& w, const Batch& bt, const veckm_event* ev
   }
   if (flow && !fused) {
     StageTimer t(c, VECKM_STAGE_MLP, stream);
-    const int rc = launch_mlp(w, c->mw, c->p.d, rows, c->num_cus, stream);
+    const int rc = launch_mlp(w, c->mw, c->p.d, rows, c->num_cus, stream, c->paper ? &c->pt : nullptr,
+                              bt.s0.W * bt.s0.H);
     if (rc) {
       if (clear) (void)launch_clear_grids(bt, w, nlines, stream);
       return rc;

@@ -741,12 +741,15 @@ __device__ inline void chunk_ksteps_p(int nsteps, const uint4* slab, UnitRing& r
           const int t0 = 2 * (kk % (NT / 2));
           const floatx4 a0 = kk < NT / 2 ? accR[mt][t0] : accI[mt][t0];
           const floatx4 a1 = kk < NT / 2 ? accR[mt][t0 + 1] : accI[mt][t0 + 1];
-          const float v[8] = {div(a0[0]), div(a0[1]), div(a0[2]), div(a0[3]),
-                              div(a1[0]), div(a1[1]), div(a1[2]), div(a1[3])};
+          float v[8] = {div(a0[0]), div(a0[1]), div(a0[2]), div(a0[3]),
+                        div(a1[0]), div(a1[1]), div(a1[2]), div(a1[3])};
           if constexpr (TERMS == 2) {
             half8 h, l;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
+              // (the fp32 value itself is split: fused into the conversions, hi
+              // and the hi that lo is taken from can round differently)
+              asm("" : "+v"(v[e]));
               h[e] = (_Float16)v[e];
               l[e] = (_Float16)(v[e] - (float)h[e]);
             }

@@ -37,6 +37,12 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 struct MlpArgs {
+  // the paper form's sums, instead of rows (k_mlp_split)
+  const float4* S;
+  const int32_t* rowvox;  // voxel of each row
+  const int32_t* nbox;    // window counts per pixel
+  const float4* ttab;     // time phases, two frequencies per entry
+  int V2;                 // pixels
   const void* x;        // U rows of K2 values, fp32 or bf16
   const float* W1;      // hidden x K2 fp32
   const uint16_t* W1b;  // hidden x K2 bf16
@@ -484,33 +490,32 @@ __global__ __launch_bounds__(NW * 64) void k_mlp_res(MlpArgs a) {
   }
 }
 
-// FP32 form with the split done once per tile: the fp32 tile lands in a
-// staging buffer, the block splits it into fp16 hi/lo pairs in a second
-// buffer (each element converted once), and the next tile's copy into the
-// staging buffer overlaps the products.  Split layout per row: chunks
-// [0, K2/8) hold the hi halves of elements 8c .. 8c + 7, chunks [K2/8, K2/4)
-// the lo halves; chunk p of row r sits at p ^ (r & 15).
+// The paper form's rows and perceptron (FP32 form) in one pass: a tile's rows
+// S(q) e^{-i A_t t} / N(q) (k_paper_rows) are formed in registers, split into
+// fp16 hi/lo pairs in LDS and multiplied; no row goes to memory and back (at
+// 0.39M rows of D = 64 the two kernels moved 600 MB and took 70 + 66 us, bound
+// by that; this one reads the 200 MB of S and t phases).  Work item: a row's 8
+// consecutive frequencies, one 64-byte read of S.  The next tile's reads are
+// in flight during the products, its rows' voxels a tile before that.  Split
+// layout per row: chunks [0, K2/8) hold the hi halves of elements 8c .. 8c + 7,
+// chunks [K2/8, K2/4) the lo halves; chunk p of row r sits at p ^ (r & 15).
 template <int NW, int NTH, int K2>
 __global__ __launch_bounds__(NW * 64) void k_mlp_split(MlpArgs a) {
   constexpr int KQ = K2 / 32;
-  constexpr int RB = K2 * 4;        // bytes per fp32 row (and per split row)
+  constexpr int RB = K2 * 4;        // bytes per split row
   constexpr int CPR = RB / 16;      // 16-byte chunks per row
-  constexpr int TILE_U4 = 64 * CPR;
-  constexpr int PFW = TILE_U4 / (NW * 64);
   constexpr int HALF = CPR / 2;     // first lo chunk of a split row
+  constexpr int FQ = K2 / 16;       // groups of 8 frequencies per row (D = K2 / 2)
+  constexpr int IT = (64 * FQ + NW * 64 - 1) / (NW * 64);  // work items per thread
   static_assert(CPR % 16 == 0 && CPR <= 64, "row size");
-  static_assert(PFW <= 63, "copies in flight exceed the wait counter");
-  static_assert((64 * HALF) % (NW * 64) == 0, "split work per thread");
   extern __shared__ __align__(16) unsigned char smem_mlp[];
-  uint4* stage = reinterpret_cast<uint4*>(smem_mlp);  // fp32 tile being copied in
-  uint4* split = stage + TILE_U4;                      // the current tile as hi/lo
+  uint4* split = reinterpret_cast<uint4*>(smem_mlp);  // the current tile as hi/lo
   __shared__ float red[NW][64][2];
   const int U = a.plan[0];
   const int ntiles = (U + 63) / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;
-  const unsigned char* X = static_cast<const unsigned char*>(a.x);
   uint4 wh[KQ][NTH], wl[KQ][NTH];
 #pragma unroll
   for (int nt = 0; nt < NTH; ++nt) {
@@ -525,35 +530,77 @@ __global__ __launch_bounds__(NW * 64) void k_mlp_split(MlpArgs a) {
   l2.load(a, wid, lane);
   const float unscale = a.unscale;
   const int mine = blockIdx.x < ntiles ? (ntiles - 1 - blockIdx.x) / gridDim.x + 1 : 0;
-  if (mine > 0) issue_tile<RB, NW>(X, blockIdx.x, U, stage, wid, lane);
+  int vox[IT], cnt[IT];
+  float4 sv[IT][4], et[IT][4];
+  auto row_of = [&](int it, int w) {  // (rows past the end repeat the last)
+    const int r = (blockIdx.x + it * gridDim.x) * 64 + (w * NW * 64 + tid) / FQ % 64;
+    return r < U ? r : U - 1;
+  };
+  auto load_vox = [&](int it) {
+#pragma unroll
+    for (int w = 0; w < IT; ++w) vox[w] = a.rowvox[row_of(it, w)];
+  };
+  auto load_sums = [&]() {  // of the rows in vox
+#pragma unroll
+    for (int w = 0; w < IT; ++w) {
+      const int f = (w * NW * 64 + tid) % FQ;
+      const int p = vox[w] % a.V2, t = vox[w] / a.V2;
+      cnt[w] = a.nbox[p];
+      // S: [D / 16][pixels][16] complex
+      const float4* s = a.S + ((int64_t)(f >> 1) * a.V2 + p) * 8 + (f & 1) * 4;
+      const float4* e = a.ttab + ((int64_t)t * (K2 / 2) + 8 * f) / 2;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        sv[w][k] = s[k];
+        et[w][k] = e[k];
+      }
+    }
+  };
+  if (mine > 0) {
+    load_vox(0);
+    load_sums();
+  }
+  if (mine > 1) load_vox(1);
   for (int it = 0; it < mine; ++it) {
     const int tile = blockIdx.x + it * gridDim.x;
-    __builtin_amdgcn_s_waitcnt(mlp_vmcnt0());
-    lds_barrier();  // tile `it` is in `stage`; `split` is free (previous products done)
-    // ---- split: work item (row r, output chunk q) covers elements 8q .. 8q + 7
+    // ---- form and split the rows (`split` is free: the last tile's products
+    //      are behind the barrier before its outputs)
 #pragma unroll
-    for (int w = 0; w < 64 * HALF / (NW * 64); ++w) {
-      const int item = w * NW * 64 + tid;
-      const int r = item / HALF, q = item % HALF;
-      const uint4 u0 = stage[r * CPR + ((2 * q) ^ (r & 15))];
-      const uint4 u1 = stage[r * CPR + ((2 * q + 1) ^ (r & 15))];
-      const float v[8] = {__uint_as_float(u0.x), __uint_as_float(u0.y), __uint_as_float(u0.z),
-                          __uint_as_float(u0.w), __uint_as_float(u1.x), __uint_as_float(u1.y),
-                          __uint_as_float(u1.z), __uint_as_float(u1.w)};
-      f16x8 hi, lo;
+    for (int w = 0; w < IT; ++w) {
+      const int item = w * NW * 64 + tid, r = item / FQ, f = item % FQ;
+      const float inv = 1.f / (float)cnt[w];
+      f16x8 rh, rl, ih, il;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        hi[e] = (_Float16)v[e];
-        lo[e] = (_Float16)(v[e] - (float)hi[e]);
+      for (int k = 0; k < 4; ++k) {
+        const float4 s = sv[w][k], e = et[w][k];
+        float re[2] = {fmaf(s.x, e.x, s.y * e.y) * inv, fmaf(s.z, e.z, s.w * e.w) * inv};
+        float im[2] = {fmaf(s.y, e.x, -s.x * e.y) * inv, fmaf(s.w, e.z, -s.z * e.w) * inv};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          // (the fp32 values themselves are split: fused into the conversions,
+          // hi and the hi that lo is taken from can round differently)
+          asm("" : "+v"(re[q]), "+v"(im[q]));
+          rh[2 * k + q] = (_Float16)re[q];
+          rl[2 * k + q] = (_Float16)(re[q] - (float)rh[2 * k + q]);
+          ih[2 * k + q] = (_Float16)im[q];
+          il[2 * k + q] = (_Float16)(im[q] - (float)ih[2 * k + q]);
+        }
       }
-      uint4 hu, lu;
-      __builtin_memcpy(&hu, &hi, 16);
-      __builtin_memcpy(&lu, &lo, 16);
-      split[r * CPR + (q ^ (r & 15))] = hu;
-      split[r * CPR + ((q + HALF) ^ (r & 15))] = lu;
+      if (item < 64 * FQ) {
+        auto put = [&](int c, f16x8 v) {
+          uint4 u;
+          __builtin_memcpy(&u, &v, 16);
+          split[r * CPR + (c ^ (r & 15))] = u;
+        };
+        put(f, rh);
+        put(FQ + f, ih);
+        put(HALF + f, rl);
+        put(HALF + FQ + f, il);
+      }
     }
-    lds_barrier();  // `split` holds the tile; `stage` is free
-    if (it + 1 < mine) issue_tile<RB, NW>(X, tile + gridDim.x, U, stage, wid, lane);
+    lds_barrier();  // `split` holds the tile
+    if (it + 1 < mine) load_sums();
+    if (it + 2 < mine) load_vox(it + 2);
     floatx4 acc[4][NTH];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
@@ -626,7 +673,7 @@ constexpr int kMlpWaves = 8;
 
 template <int NTH4, int K2>
 static int launch_split(const MlpArgs& a, int num_cus, hipStream_t s) {
-  constexpr size_t lds = 2 * (size_t)64 * K2 * 4;
+  constexpr size_t lds = (size_t)64 * K2 * 4;
   if constexpr (kMlpWaves == 8 && NTH4 % 2 == 0)
     return launch_lds(k_mlp_split<8, NTH4 / 2, K2>, a, lds, 1, num_cus, s, 512);
   else
@@ -691,8 +738,14 @@ bool mlp_rows_split(int d, int hidden) {
 }
 
 int launch_mlp(const Workspace& w, const MlpWeights& mw, int d, int rows, int num_cus,
-               void* stream) {
+               void* stream, const PaperTables* pt, int pixels) {
+  if (rows == kRowsSplit16 && !pt) return VECKM_E_INVAL;
   MlpArgs a;
+  a.S = reinterpret_cast<const float4*>(w.S);
+  a.rowvox = w.rowvox;
+  a.nbox = w.nbox;
+  a.ttab = pt ? reinterpret_cast<const float4*>(pt->ttab) : nullptr;
+  a.V2 = pixels;
   a.x = w.rows;
   a.W1 = mw.W1;
   a.W1b = mw.W1b;

@@ -248,7 +248,8 @@ __global__ void k_boxy(int W, int H, int ry, const int32_t* __restrict__ c,
   out[p] = s;
 }
 
-// The rows of the query voxels, row = S(q) e^{-i A_t t} / N(q): D / 4 lanes
+// The rows of the query voxels (encodings handed out, bf16 rows, and widths the
+// split perceptron does not take), row = S(q) e^{-i A_t t} / N(q): D / 4 lanes
 // per row, each with four consecutive frequencies; every lane group takes two
 // rows.  Rows past the device-side row count plan[0] are skipped.
 template <bool BF16>
@@ -354,7 +355,7 @@ int launch_paper_encode(const Batch& bt, const Workspace& w, const PaperTables& 
   // rows: at most one per query (the row count itself is on the device)
   const float2* S = reinterpret_cast<const float2*>(w.S);
   const int per_block = 2 * 4 * (64 / (D / 4));
-  if (bt.m > 0) {
+  if (bt.m > 0 && rows != kRowsSplit16) {  // (else the perceptron forms them)
     if (rows == kRowsBF16)
       hipLaunchKernelGGL(k_paper_rows<true>, dim3(blocks(bt.m, per_block)), dim3(256), 0, s, sl.W,
                          sl.H, D, w.plan, w.rowvox, S, w.nbox, ttab, w.rows);

@@ -220,7 +220,8 @@ struct EncodeTables {
 // the perceptron forms that read them.
 constexpr int kRowsF32 = 0;      // fp32 rows; perceptron on fp32 matrix cores
 constexpr int kRowsBF16 = 1;     // bf16 rows; bf16 perceptron (FP16 form)
-constexpr int kRowsSplit16 = 2;  // fp32 rows split into fp16 hi/lo in the perceptron (FP32 form)
+constexpr int kRowsSplit16 = 2;  // the paper form's: no rows, the perceptron forms and splits them
+                                 // into fp16 hi/lo (FP32 form)
 constexpr int kRowsHiLo16 = 3;   // rows written as fp16 hi/lo pairs by the encoder: each group of
                                  // 4 consecutive elements is a 16-byte unit [hi x 4, lo x 4]
                                  // (FP32 form)
@@ -277,8 +278,10 @@ int launch_encode(const Batch& bt, const Workspace& w, const EncodeTables& et, i
 // else found from each query's voxel (`queries` as in the call, or NULL).
 int launch_expand_emb(const Batch& bt, const Workspace& w, const int32_t* queries,
                       const Brick& b, bool use_qmap, int d, float* emb, void* stream);
+// (kRowsSplit16: the paper form's rows are formed here, from its sums over
+// `pixels` pixels)
 int launch_mlp(const Workspace& w, const MlpWeights& mw, int d, int rows, int num_cus,
-               void* stream);
+               void* stream, const PaperTables* pt = nullptr, int pixels = 0);
 // Whether the FP32-form perceptron runs on fp16 hi/lo operand pairs for
 // this shape (W1 fragments fit in registers); else on the fp32 matrix cores.
 bool mlp_rows_split(int d, int hidden);
