@@ -666,6 +666,41 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(int ntiles, int nb,
                                                              int32_t* __restrict__ plan) {
   __shared__ int sums[kScanNV][kScanThreads];
   const int tid = threadIdx.x;
+  auto finish = [&](int whole, int chunked, int ud, int us) {
+    const int per_item = single_rows_per_item(us, whole, sr);
+    off[nb] = ud + us;
+    plan[0] = ud + us;
+    plan[1] = 0;
+    plan[2] = whole + (us + per_item - 1) / per_item;
+    plan[3] = ud;
+    plan[4] = whole;
+    plan[5] = per_item;
+    plan[6] = chunked;
+  };
+  if (ntiles <= 64) {
+    // (up to half a million bricks) one wave, a tile per lane, no barriers:
+    // 11 us in the general form, most of it 20 barriers of 16 waves
+    if (tid >= 64) return;
+    int at = 0, chunked = 0, totals[kScanNV];
+#pragma unroll
+    for (int k = 0; k < kScanNV; ++k) {
+      const int own = tid < ntiles ? part[tid * kScanNV + k] : 0;
+      int inc = own;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(inc, d);
+        if (tid >= d) inc += t;
+      }
+      totals[k] = __shfl(inc, 63);
+      if (k == kScanClasses - 1) chunked = at;
+      // classes one after another; whole bricks' rows from 0, single rows after
+      const int first = k < kScanClasses ? at : k == kRowsD ? 0 : totals[kRowsD];
+      if (k < kScanClasses) at += totals[k];
+      if (tid < ntiles) part[tid * kScanNV + k] = first + inc - own;
+    }
+    if (tid == 0) finish(at, chunked, totals[kRowsD], totals[kRowsS]);
+    return;
+  }
   const int per = (ntiles + kScanThreads - 1) / kScanThreads;
   const int s0 = min(tid * per, ntiles), s1 = min(s0 + per, ntiles);
   int v[kScanNV];
@@ -705,17 +740,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(int ntiles, int nb,
       part[i * kScanNV + k] = run[k];
       run[k] += t;
     }
-  if (tid == 0) {
-    const int per_item = single_rows_per_item(us, acc, sr);
-    off[nb] = ud + us;
-    plan[0] = ud + us;
-    plan[1] = 0;
-    plan[2] = acc + (us + per_item - 1) / per_item;
-    plan[3] = ud;
-    plan[4] = acc;
-    plan[5] = per_item;
-    plan[6] = start[kScanClasses - 1];
-  }
+  if (tid == 0) finish(acc, start[kScanClasses - 1], ud, us);
 }
 
 // ONE = true: the bricks fit in one tile, and this single block does the
