@@ -217,8 +217,8 @@ int veckm_flow_batch(veckm_ctx* ctx, const veckm_slice* slices, int32_t count,
      346 x 260 sensor with 25 bins and 20k events at D = 64 needs 47 MB);
      beyond that it returns VECKM_E_BUDGET and launches nothing.
      Sharing: every call on one GPU uses the same array and finds it as the
-     last call left it (the count and pair grids and the row flags are
-     cleared at the start of each call).
+     last call left it (the count grid and the row flags are cleared at
+     the start of each call).
      Calls that overlap on one GPU, on any streams or contexts or threads,
      race and give undefined results: serialise them (one stream, or
      synchronise between calls).

@@ -375,10 +375,9 @@ int run(veckm_ctx* c, const Workspace& w, const Batch& bt, const veckm_event* ev
                    : c->paper                          ? kRowsSplit16
                                                       : kRowsHiLo16;
   // slice calls (not the paper form; a window's counts are resident) find
-  // the count grid, the pair grid and the row flags zero and leave them
-  // zero: the ranking kernel clears the flags, and after the expansion the
-  // events' voxels are cleared; a call whose launches fail clears all three
-  // grids densely
+  // the count grid and the row flags zero and leave them zero: the ranking
+  // kernel clears the flags, and after the expansion the events' voxels are
+  // cleared; a call whose launches fail clears both densely
   const bool clear = !c->paper && !c->window;
   const int64_t nlines = (int64_t)bt.nbricks * c->et.brick.by * c->et.brick.bt;
   {
@@ -1224,8 +1223,8 @@ int veckm_flow_noalloc(veckm_ctx* ctx, const veckm_event* events, int64_t n, int
   rc = scratch_on(ctx->device, &base);
   if (rc) return rc;
   carve_noalloc(ctx, bt, base, &w);
-  // the array holds whatever the last call left: the count and pair grids
-  // and the row flags start at zero (fill kernels, no memset)
+  // the array holds whatever the last call left: the count grid and the row
+  // flags start at zero (fill kernels, no memset)
   rc = launch_clear_grids(bt, w, bt.nbricks * (int64_t)ctx->et.brick.by * ctx->et.brick.bt,
                           stream);
   if (rc) return rc;

@@ -256,17 +256,11 @@ __global__ __launch_bounds__(256) void k_rank(Batch bt, Brick b, const int32_t* 
 // LDS, in row order, and clears their flags (the last reader; a brick
 // without a flagged row only writes its zero row count).  Then it walks the
 // listed rows, 64 / bx of them per step (a lane per voxel), in groups of
-// kG steps: each lane issues the group's loads (its count, and the count
-// beside it that the pair entries need: left of a row's first voxel, right
-// of its last) before using any.  A brick's rows hold a few tens of events
+// kG steps: each lane issues the group's loads before using any.  A brick's rows hold a few tens of events
 // in sparse calls, so most of its rows are not visited at all and the wave
 // waits on few rounds of loads.  Rows are listed in order and a row's
 // voxels are consecutive lanes, so the wave numbers the query voxels in
-// brick-local voxel order (as k_rank_lines4 does).  The pair grid is all
-// zero between such calls (k_clear_events returns it there), so only the
-// entries a flagged row touches are written: entry x of each of its voxels,
-// and entry x + 1 of its last voxel in the slice (which the neighbouring
-// brick may also write, with the same value: both read the final counts).
+// brick-local voxel order (as k_rank_lines4 does).
 // A flagged row lies inside the slice (flags come from valid events only);
 // its voxels beyond the slice's x edge are skipped.  Dynamic LDS: 4 waves x
 // by x bt row numbers (uint16).
@@ -1132,11 +1126,10 @@ int launch_prepare(const Batch& bt, const Workspace& w, const veckm_event* ev,
   // (a brick has at most kMaxBrickVoxels / 4 rows of flags; a step of the
   // ranking kernels holds whole rows)
   if (pairs && (et.brick.bx < 4 || et.brick.bx > 64)) return VECKM_E_INVAL;
-  // slice calls (not the paper form) find the count grid, the pair grid and
-  // the row flags zero: every such call returns them to zero after use (the
-  // ranking kernel clears the flags, launch_clear_events the rest; all three
-  // are zeroed once at context creation); the paper form clears the count
-  // grid here
+  // slice calls (not the paper form) find the count grid and the row flags
+  // zero: every such call returns them to zero after use (the ranking kernel
+  // clears the flags, launch_clear_events the counts; both are zeroed once at
+  // context creation); the paper form clears the count grid here
   if (!pairs)
     hipLaunchKernelGGL(k_fill_i32, dim3(fill_grid(bt.nvox)), dim3(256), 0, s, w.count, bt.nvox, 0);
   if (bt.n > 0)
