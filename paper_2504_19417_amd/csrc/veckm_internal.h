@@ -76,8 +76,8 @@ constexpr int kSparseTag = 1 << 30;
 // Bricks with fewer rows than this go to the encoder row by row.  A full chunk
 // of single rows costs about 1.2 of a brick's, a brick's chunk costs its box
 // and the better part of a full chunk's time however few rows it holds.  Whole
-// call with 64 / 128 / 192: 64 lognormal slices 5.33 / 4.90 / 4.95 ms, 5M-event
-// slice 2.71 / 2.68 / 2.78 ms, 50k events encoded 0.140 / 0.124 / 0.123 ms.
+// call with 80 / 128 / 176: 64 lognormal slices 4.59 / 4.41 / 4.44 ms, 5M-event
+// slice 2.54 / 2.54 / 2.61 ms, 1M-event slice (FP16 form) 0.359 / 0.358 / 0.365 ms.
 constexpr int kSparseBelow = 128;
 std::vector<Tiling> tiling_candidates(int rx, int ry, int rt, int d, int precision, int kp);
 size_t encode_lds_need(int d, int precision, int nbuf, int kp, int vol, int layout = 0);
