@@ -82,7 +82,6 @@ struct veckm_ctx {
   bool started = false;
   int32_t tref = 0;
   int64_t wend = 0;
-  int bits_tiling = 0;  // the tiling whose order the ring's bits lie in
   PaperTables pt;
   int max_slices = 1;
   std::vector<void*> allocs;
@@ -670,7 +669,7 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
   et.wts = dwts;
   for (size_t i = 0; i < tl.size(); ++i) {
     EncodeTables t = et;
-    t.brick = tl[i].brick;
+    t.brick = t.bits = tl[i].brick;
     t.nbuf = tl[i].nbuf;
     t.layout = tl[i].layout;
     t.runs = druns[i];
@@ -800,8 +799,9 @@ int veckm_window_create(const veckm_params* params, veckm_ctx** out) {
   int rc = veckm_create(params, &c);
   if (rc) return rc;
   c->window = true;
-  // an empty window: every plane of the ring holds zero counts (and bits, in
-  // any tiling's order)
+  for (EncodeTables& t : c->tilings) t.bits = c->tilings[0].brick;
+  c->et = c->tilings[0];
+  // an empty window: every plane of the ring holds zero counts and bits
   const int64_t V = (int64_t)params->width * params->height * params->max_bins;
   if (hipMemset(c->w.count, 0, (size_t)V * 4) != hipSuccess ||
       hipMemset(c->w.ulist, 0, (size_t)c->w.umax * 4) != hipSuccess ||
@@ -811,15 +811,6 @@ int veckm_window_create(const veckm_params* params, veckm_ctx** out) {
   }
   *out = c;
   return VECKM_OK;
-}
-
-// The ring's bits lie in the order of the tiling in use: rebuilt whole after
-// another one was selected.
-static int window_bits(veckm_ctx* c, const Batch& bt, void* stream) {
-  if (c->bits_tiling == c->tiling) return VECKM_OK;
-  const int rc = launch_window_bits(c->w, bt, c->et.brick, 0, c->p.max_bins, stream);
-  if (!rc) c->bits_tiling = c->tiling;
-  return rc;
 }
 
 int veckm_window_push(veckm_ctx* ctx, const veckm_event* events, int64_t n, int32_t t0,
@@ -833,11 +824,8 @@ int veckm_window_push(veckm_ctx* ctx, const veckm_event* events, int64_t n, int3
   const int64_t wend0 = ctx->started ? ctx->wend : (int64_t)t0;
   const int64_t end = (int64_t)t0 + nbins;
   const int64_t b0 = end - T > wend0 ? end - T : wend0;  // bins entering the window
-  Batch bt{};
-  bt.s0 = describe(ctx, ctx->p.width, ctx->p.height, T, 0, 0, 0, 0, 0, n);
-  int rc = launch_window_push(ctx->w, events, n, bt, ctx->et.brick, t0, nbins, tref, b0,
-                              (int)(end - b0), stream);
-  if (!rc) rc = window_bits(ctx, bt, stream);
+  const int rc = launch_window_push(ctx->w, events, n, ctx->p.width, ctx->p.height, T, ctx->et.bits,
+                                    t0, nbins, tref, b0, (int)(end - b0), stream);
   if (rc) return rc;
   ctx->started = true;
   ctx->tref = tref;
@@ -873,8 +861,7 @@ int window_batch(veckm_ctx* c, const veckm_event* queries, int64_t m, const void
 int veckm_window_encode(veckm_ctx* ctx, const veckm_event* queries, int64_t m, float* emb,
                         void* stream) {
   Batch bt;
-  int rc = window_batch(ctx, queries, m, emb, &bt);
-  if (!rc) rc = window_bits(ctx, bt, stream);
+  const int rc = window_batch(ctx, queries, m, emb, &bt);
   if (rc) return rc;
   return run(ctx, ctx->w, bt, queries, nullptr, emb, nullptr, stream);
 }
@@ -882,11 +869,9 @@ int veckm_window_encode(veckm_ctx* ctx, const veckm_event* queries, int64_t m, f
 int veckm_window_flow(veckm_ctx* ctx, const veckm_event* queries, int64_t m, float* flow,
                       void* stream) {
   Batch bt;
-  int rc = window_batch(ctx, queries, m, flow, &bt);
+  const int rc = window_batch(ctx, queries, m, flow, &bt);
   if (rc) return rc;
   if (ctx->mw.hidden == 0) return VECKM_E_STATE;
-  rc = window_bits(ctx, bt, stream);
-  if (rc) return rc;
   return run(ctx, ctx->w, bt, queries, nullptr, nullptr, flow, stream);
 }
 

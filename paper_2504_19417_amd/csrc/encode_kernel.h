@@ -49,6 +49,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 struct EncArgs {
   Batch bt;
   Brick b;
+  Brick bb;              // of the bits (EncodeTables::bits)
   int rx, ry, rt;
   int K, nsteps;
   int SX, SY, ST, vol;
@@ -1029,8 +1030,9 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         const int tp = t + sl.tshift < sl.T ? t + sl.tshift : t + sl.tshift - sl.T;
         uint32_t* rb = rbits + r * rstride;
         uint16_t* out = reinterpret_cast<uint16_t*>(rb);
-        const int nl = a.b.by * a.b.bt, sx = __builtin_ctz(a.b.bx), sy = __builtin_ctz(a.b.by),
-                  stt = __builtin_ctz(a.b.bt);
+        const int nl = a.bb.by * a.bb.bt, sx = __builtin_ctz(a.bb.bx), sy = __builtin_ctz(a.bb.by),
+                  stt = __builtin_ctz(a.bb.bt);
+        const int nbx = (sl.W + a.bb.bx - 1) >> sx, nby = (sl.H + a.bb.by - 1) >> sy;
         const int nc = (a.rx + 4) >> 2, nr = (2 * a.rx + 4) >> 2;  // runs of the centre / other rows
         const int ny = 2 * a.ry + 1, nwr = 1 + a.ry + a.rt * ny;
         if (part == 0) {
@@ -1045,8 +1047,8 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         // address is the row's own brick's plus 24-bit steps of bricks, columns
         // and x rows; outside the slice any word is read and masked (no branch,
         // so that loads are not serialised).
-        const int tb = tp >> stt, yb = y >> sy, xb = x >> sx, plane = sl.nbx * sl.nby;
-        const uint2* own = a.bits + (int64_t)(sl.brick_off + (tb * sl.nby + yb) * sl.nbx + xb) * nl;
+        const int tb = tp >> stt, yb = y >> sy, xb = x >> sx, plane = nbx * nby;
+        const uint2* own = a.bits + (int64_t)(sl.brick_off + (tb * nby + yb) * nbx + xb) * nl;
         struct Line {
           int off;
           bool in;
@@ -1054,12 +1056,12 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         auto line = [&](int dy, int dt) -> Line {
           const int yy = y + dy, tt = t + dt;
           const int pl = tt + sl.tshift < sl.T ? tt + sl.tshift : tt + sl.tshift - sl.T;
-          const int step = __mul24((pl >> stt) - tb, plane) + __mul24((yy >> sy) - yb, sl.nbx);
-          return {(step << (sy + stt)) + ((pl & (a.b.bt - 1)) << sy) + (yy & (a.b.by - 1)),
+          const int step = __mul24((pl >> stt) - tb, plane) + __mul24((yy >> sy) - yb, nbx);
+          return {(step << (sy + stt)) + ((pl & (a.bb.bt - 1)) << sy) + (yy & (a.bb.by - 1)),
                   (bool)(((unsigned)yy < (unsigned)sl.H) & ((unsigned)tt < (unsigned)sl.T))};
         };
         auto word = [&](Line ln, int cx) -> uint2 {
-          const bool in = ln.in & ((unsigned)cx < (unsigned)sl.nbx);
+          const bool in = ln.in & ((unsigned)cx < (unsigned)nbx);
           const uint2 v = own[in ? ln.off + ((cx - xb) << (sy + stt)) : 0];
           return make_uint2(in ? v.x : 0u, in ? v.y : 0u);
         };
@@ -1084,7 +1086,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
           dt = u < 0 ? 0 : 1 + u / ny;
           dy = u < 0 ? w : u % ny - a.ry;
         };
-        if (a.b.bx == 32) {
+        if (a.bb.bx == 32) {
           // two words hold a run row of up to 28 voxels; several window rows
           // at a time, all loads first
           constexpr int kB = NW >= 16 ? 4 : 8;
@@ -1120,11 +1122,11 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
             window(w, dx, dy, dt, first, n);
             auto cut = [&](int x0, Line ln) {
               uint64_t o = 0, m = 0;
-              const int cx = x0 >> sx, sh = x0 & (a.b.bx - 1);
-              for (int k = 0; k * a.b.bx < sh + 4 * n; ++k) {
+              const int cx = x0 >> sx, sh = x0 & (a.bb.bx - 1);
+              for (int k = 0; k * a.bb.bx < sh + 4 * n; ++k) {
                 const uint2 v = word(ln, cx + k);
-                o |= (uint64_t)v.x << (k * a.b.bx);
-                m |= (uint64_t)v.y << (k * a.b.bx);
+                o |= (uint64_t)v.x << (k * a.bb.bx);
+                m |= (uint64_t)v.y << (k * a.bb.bx);
               }
               return make_uint2((uint32_t)(o >> sh), (uint32_t)(m >> sh));
             };

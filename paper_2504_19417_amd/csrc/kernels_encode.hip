@@ -48,7 +48,7 @@ static int dispatch_nt(const EncArgs& a, const EncodeTables& et, int rows, int n
 }
 
 int encode_single_rows(const EncodeTables& et) {
-  if (et.brick.bx > 32) return 0;  // (a brick x row's bits are one word)
+  if (et.bits.bx > 32) return 0;  // (a brick x row's bits are one word)
   // (in the box's space: the bit table, and a head and the bits of each row)
   const int room = box_dwords(et.brick, et.rx, et.ry, et.rt) * 4 - kLutDwords * 4;
   const int fit = room / (16 + 4 * single_row_dwords(et.KP / kKStep));
@@ -93,6 +93,7 @@ int launch_encode(const Batch& bt, const Workspace& w, const EncodeTables& et, i
   }
   a.bt = bt;
   a.b = et.brick;
+  a.bb = et.bits;
   a.rx = et.rx;
   a.ry = et.ry;
   a.rt = et.rt;

@@ -140,23 +140,24 @@ __device__ inline void put_bits(int count, bool valid, uint2* at, int lane, int 
 // while ranking): the bits of their brick x rows (bins counted as planes), the
 // pair entries of voxels of 3 or more events, and the check of the counts.  A
 // wave per 64 voxels of an x row, strided over the planes' rows.
-__global__ __launch_bounds__(256) void k_bits(SliceDesc s, Brick b, int p0, int np,
+__global__ __launch_bounds__(256) void k_bits(int W, int H, Brick b, int p0, int np,
                                               const int32_t* __restrict__ count,
                                               uint32_t* __restrict__ pairs,
                                               uint2* __restrict__ bits, int32_t* __restrict__ err) {
   const int lane = threadIdx.x & 63;
   const int sx = __builtin_ctz(b.bx), sy = __builtin_ctz(b.by), st = __builtin_ctz(b.bt);
-  const int per_row = (s.W + 63) >> 6, total = np * s.H * per_row;
+  const int nbx = (W + b.bx - 1) >> sx, nby = (H + b.by - 1) >> sy;
+  const int per_row = (W + 63) >> 6, total = np * H * per_row;
   bool bad = false;
   for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < total; i += gridDim.x * 4) {
     const int x = (i % per_row) * 64 + lane, r = i / per_row;
-    const int y = r % s.H, p = p0 + r / s.H;
-    const int32_t* c = count + ((int64_t)p * s.H + y) * s.W + x;
-    const int hi = x < s.W ? *c : 0;
+    const int y = r % H, p = p0 + r / H;
+    const int32_t* c = count + ((int64_t)p * H + y) * W + x;
+    const int hi = x < W ? *c : 0;
     bad |= hi > VECKM_MAX_VOXEL_EVENTS;
-    if (hi > 2) put_pairs(c, x, s.W, hi, pairs + ((int64_t)p * s.H + y) * (s.W + 1));
-    const int64_t brick = ((int64_t)(p >> st) * s.nby + (y >> sy)) * s.nbx + (x >> sx);
-    put_bits(hi, x < s.W,
+    if (hi > 2) put_pairs(c, x, W, hi, pairs + ((int64_t)p * H + y) * (W + 1));
+    const int64_t brick = ((int64_t)(p >> st) * nby + (y >> sy)) * nbx + (x >> sx);
+    put_bits(hi, x < W,
              bits + brick * (b.by * b.bt) + (((p & (b.bt - 1)) << sy) | (y & (b.by - 1))), lane, b.bx);
   }
   if (bad) atomicOr(err, kErrOverflow);
@@ -1152,19 +1153,9 @@ int launch_prepare(const Batch& bt, const Workspace& w, const veckm_event* ev,
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
 
-int launch_window_bits(const Workspace& w, const Batch& bt, const Brick& b, int p0, int np,
+int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, int W, int H, int T,
+                       const Brick& bits, int t0, int nbins, int tref, int64_t clear_b0, int clear_nb,
                        void* stream) {
-  const int64_t waves = (int64_t)np * bt.s0.H * ((bt.s0.W + 63) / 64);
-  const int64_t blocks = std::min<int64_t>(8192, (waves + 3) / 4);
-  hipLaunchKernelGGL(k_bits, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, bt.s0, b, p0,
-                     np, w.count, w.pairs, reinterpret_cast<uint2*>(brick_bits(w)), w.err);
-  return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
-}
-
-int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, const Batch& bt,
-                       const Brick& b, int t0, int nbins, int tref, int64_t clear_b0, int clear_nb,
-                       void* stream) {
-  const int W = bt.s0.W, H = bt.s0.H, T = bt.s0.T;
   hipStream_t s = (hipStream_t)stream;
   const int64_t plane = (int64_t)W * H;
   // the planes of the bins that enter the window: clear them, count the new
@@ -1182,8 +1173,10 @@ int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, con
                        w.count, w.err);
   for (const auto& sp : span)
     if (sp[1] > 0) {
-      const int rc = launch_window_bits(w, bt, b, sp[0], sp[1], stream);
-      if (rc) return rc;
+      const int64_t waves = (int64_t)sp[1] * H * ((W + 63) / 64);
+      hipLaunchKernelGGL(k_bits, dim3((unsigned)std::min<int64_t>(8192, (waves + 3) / 4)), dim3(256), 0, s,
+                         W, H, bits, sp[0], sp[1], w.count, w.pairs,
+                         reinterpret_cast<uint2*>(brick_bits(w)), w.err);
     }
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }

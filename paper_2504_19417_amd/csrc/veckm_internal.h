@@ -182,10 +182,11 @@ struct Workspace {
 
 // The brick-local voxels of each brick's ranks (bricks x brick volume).
 inline uint16_t* ulist_of(const Workspace& w) { return reinterpret_cast<uint16_t*>(w.ulist); }
-// Per brick x row of a bounded-window slice call (bricks x (by bt), bx <= 32):
-// two words, bit x of which are the low and the high bit of voxel x's count (3
-// for 3 and more events).  (8 bytes per bx >= 4 voxels: within the 2 bytes
-// per voxel behind the lists.)  Written whole by the ranking kernels.
+// Per brick x row of a bounded-window call (bricks x (by bt), bx <= 32; the
+// bricks are EncodeTables::bits): two words, bit x of which are the low and the
+// high bit of voxel x's count (3 for 3 and more events).  (8 bytes per bx >= 4
+// voxels: within the 2 bytes per voxel behind the lists.)  Written whole by a
+// slice call's ranking kernels, plane by plane by a window's pushes.
 inline uint32_t* brick_bits(const Workspace& w) {
   return reinterpret_cast<uint32_t*>(ulist_of(w) + w.umax);
 }
@@ -213,6 +214,10 @@ struct EncodeTables {
   int layout = 0;  // encoder wave layout (Tiling::layout)
   int rx = 0, ry = 0, rt = 0;
   Brick brick{32, 16, 8};
+  // the brick whose x rows a call's bits are kept by (brick_bits): `brick` in
+  // slice calls, which write them whole; in a sliding window, whose bits stay
+  // from push to push, the first tiling's whichever is selected
+  Brick bits{32, 16, 8};
   int d = 0;
 };
 
@@ -313,11 +318,9 @@ int launch_take_err(const Workspace& w, int32_t* host, void* stream);
 // T planes (bin b in plane (b - tref) mod T, clear_nb <= T); the events of
 // bins [t0, t0 + nbins) among them are counted.  Then an encode of query
 // events against the resident window (bt describes the window, tshift set).
-int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, const Batch& bt,
-                       const Brick& b, int t0, int nbins, int tref, int64_t clear_b0, int clear_nb,
-                       void* stream);
-// Rebuilds what ranking keeps per brick x row of ring planes [p0, p0 + np).
-int launch_window_bits(const Workspace& w, const Batch& bt, const Brick& b, int p0, int np,
+// (`bits`: EncodeTables::bits)
+int launch_window_push(const Workspace& w, const veckm_event* ev, int64_t n, int W, int H, int T,
+                       const Brick& bits, int t0, int nbins, int tref, int64_t clear_b0, int clear_nb,
                        void* stream);
 int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event* queries,
                           const EncodeTables& et, int num_cus, void* stream);
