@@ -675,7 +675,9 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
     t.runs = druns[i];
     t.runs1 = druns1;
     t.rs = encode_single_rows(t);
-    t.sp = druns1 && t.rs >= 16 ? kSparseBelow : 0;
+    t.sp = druns1 && t.rs >= 16 && single_rows_fit(params->width, params->height, t.bits)
+               ? kSparseBelow
+               : 0;
     c->tilings.push_back(t);
   }
   c->et = c->tilings[0];
@@ -799,7 +801,10 @@ int veckm_window_create(const veckm_params* params, veckm_ctx** out) {
   int rc = veckm_create(params, &c);
   if (rc) return rc;
   c->window = true;
-  for (EncodeTables& t : c->tilings) t.bits = c->tilings[0].brick;
+  for (EncodeTables& t : c->tilings) {
+    t.bits = c->tilings[0].brick;
+    if (!single_rows_fit(params->width, params->height, t.bits)) t.sp = 0;
+  }
   c->et = c->tilings[0];
   // an empty window: every plane of the ring holds zero counts and bits
   const int64_t V = (int64_t)params->width * params->height * params->max_bins;

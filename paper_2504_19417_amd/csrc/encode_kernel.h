@@ -1045,7 +1045,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         }
         // The words of the window row at (y + dy, t + dt), brick column cx.  The
         // address is the row's own brick's plus 24-bit steps of bricks, columns
-        // and x rows; outside the slice any word is read and masked (no branch,
+        // and x rows (single_rows_fit); outside the slice any word is read and masked (no branch,
         // so that loads are not serialised).
         const int tb = tp >> stt, yb = y >> sy, xb = x >> sx, plane = nbx * nby;
         const uint2* own = a.bits + (int64_t)(sl.brick_off + (tb * nby + yb) * nbx + xb) * nl;

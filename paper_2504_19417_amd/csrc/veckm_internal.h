@@ -86,6 +86,13 @@ struct EncodeTables;
 // Single rows the encoder takes per item at most (a chunk whose row records
 // fit in the space of the brick's box).
 int encode_single_rows(const EncodeTables& et);
+// Whether the encoder may collect single rows on a W x H sensor whose bits lie by
+// the bricks b: it steps between the bricks of a row's window with signed 24-bit
+// products (a full-rate instruction, a 32-bit product takes four times as long)
+// by the bricks of an x row and of a plane, so a plane has fewer than 2^23.
+inline bool single_rows_fit(int W, int H, const Brick& b) {
+  return (int64_t)((W + b.bx - 1) / b.bx) * ((H + b.by - 1) / b.by) < (int64_t)1 << 23;
+}
 int encode_waves(int layout = 0);  // waves per encoder block
 int lds_volume_halves(const Brick& b, int rx, int ry, int rt);
 // The encoder's LDS box of a brick: the brick plus the window halo, widened
