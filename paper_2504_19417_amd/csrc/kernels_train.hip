@@ -17,7 +17,8 @@
 //   k_train_end  the partial sums and the update
 //
 // Both contractions run on the bf16 matrix cores at fp32 accuracy: an fp32
-// operand is the exact sum of three bf16 terms (h + m + l, 8 bits each), and
+// operand of ordinary size is the exact sum of three bf16 terms (h + m + l, 8
+// bits each; the usual expansion of a number into non-overlapping parts), and
 // the products hh, hm, mh, mm, hl, lh keep everything above 2^-26 of a
 // product; sums are fp32.  Six bf16 products of a 32 x 32 x 16 tile take 192
 // cycles of a SIMD's matrix core, the eight fp32 products of that tile 512.
@@ -25,9 +26,11 @@
 // (0.93 PFLOP/s of bf16 products; a large bf16 GEMM reaches 1.2 on this card),
 // k_train_end 18 us, against 6.5 ms per step for fp32 vector-ALU GEMMs with H
 // stored; the error against 64 bits is the same.
-// A tile whose operands hold an infinity, a NaN or a value beyond the bf16
-// range (|v| >= 2^127) is computed again on the fp32 matrix cores, which
-// treat those as fp32 arithmetic does.
+// A tile whose operands hold a value that three bf16 terms do not carry is
+// computed again on the fp32 matrix cores, which treat it as fp32 arithmetic
+// does: an infinity, a NaN, |v| >= 2^127 (h may round to infinity), or 0 < |v|
+// < 2^-110 (its last bit lies under bf16's smallest number, 2^-133, so l would
+// lose bits; both matrix cores keep subnormal operands, products and sums).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,15 +44,26 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr uint32_t kHuge = 0x7f000000u;  // 2^127
+constexpr uint32_t kTiny = 0x08800000u;  // 2^-110
 
-// The three bf16 terms of 8 fp32 values; `big` collects their magnitudes' bits.
+// The extent of the magnitudes seen (as bits; a zero counts as neither end).
+struct Extent {
+  uint32_t big = 0, low = ~0u;
+  __device__ inline void take(float v) {
+    const uint32_t mag = __float_as_uint(v) & 0x7fffffffu;
+    big = mag > big ? mag : big;
+    low = mag - 1 < low ? mag - 1 : low;
+  }
+  __device__ inline bool beyond_terms() const { return big >= kHuge || low < kTiny - 1; }
+};
+
+// The three bf16 terms of 8 fp32 values, and what those values extend over.
 struct Split8 {
   bf16x8 t[3];
-  __device__ inline void make(const float (&v)[8], uint32_t& big) {
+  __device__ inline void make(const float (&v)[8], Extent& ext) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const uint32_t mag = __float_as_uint(v[e]) & 0x7fffffffu;
-      big = mag > big ? mag : big;
+      ext.take(v[e]);
       const __bf16 h = (__bf16)v[e];
       const float r1 = v[e] - (float)h;
       const __bf16 m = (__bf16)r1;
@@ -73,7 +87,9 @@ __device__ inline floatx16 mfma_split(const bf16x8 (&a)[3], const bf16x8 (&b)[3]
 // W1's fragments (the B operand of layer 1): per 16-feature k-step, 32-unit
 // tile and bf16 term, lane l holds features 8 (l >> 5) + (0..7) of unit l & 31.
 __device__ inline void put_w1_frag(uint16_t* frag, int nt, int hid, int k, float w, int* bad) {
-  if ((__float_as_uint(w) & 0x7fffffffu) >= kHuge) *bad = 1;  // (stays set: layer 1 runs in fp32)
+  Extent ext;
+  ext.take(w);
+  if (ext.beyond_terms()) *bad = 1;  // (stays set: layer 1 runs in fp32)
   const __bf16 h = (__bf16)w;
   const float r1 = w - (float)h;
   const __bf16 m = (__bf16)r1;
@@ -193,14 +209,14 @@ __global__ __launch_bounds__(NW * 64) void k_train_fwd(FwdArgs a) {
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[nt][i] = 0.f;
-    uint32_t big = 0;
+    Extent ext;
 #pragma unroll 1
     for (int ks = 0; ks < a.ksteps; ++ks) {
       float xv[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) xv[e] = xn[e];
       Split8 xs;
-      xs.make(xv, big);
+      xs.make(xv, ext);
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this step's slab has landed
       lds_barrier();
       const bool more = ks + 1 < a.ksteps;
@@ -220,7 +236,7 @@ __global__ __launch_bounds__(NW * 64) void k_train_fwd(FwdArgs a) {
       }
       buf ^= 1;
     }
-    if (__any(big >= kHuge) || *a.bad) {  // the wave's rows again in fp32
+    if (__any(ext.beyond_terms()) || *a.bad) {  // the wave's rows again in fp32
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -375,14 +391,14 @@ __global__ __launch_bounds__(512) void k_train_dw1(int64_t M, int k2, int hidden
       }
     }
   };
-  uint32_t big = 0;
+  Extent ext;
   auto stage = [&](int buf) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int tile = wid + 8 * u;
       if (tile < TILES) {
         Split8 s;
-        s.make(v[u], big);
+        s.make(v[u], ext);
 #pragma unroll
         for (int t = 0; t < 3; ++t) __builtin_memcpy(&frag[buf][(tile * 3 + t) * 64 + lane], &s.t[t], 16);
       }
@@ -422,7 +438,7 @@ __global__ __launch_bounds__(512) void k_train_dw1(int64_t M, int k2, int hidden
     if (more) stage((int)((s + 1) & 1));
     lds_barrier();
   }
-  if (big >= kHuge) redo = 1;
+  if (ext.beyond_terms()) redo = 1;
   __syncthreads();
   if (redo) {  // the tile again in fp32
     for (int i = 0; i < TA; ++i)

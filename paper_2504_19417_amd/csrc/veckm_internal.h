@@ -348,7 +348,7 @@ struct TrainState {
   float* head_part = nullptr;  // head_blocks x (3 hidden + 3)
   float* w1_part = nullptr;    // row splits x hidden x k2
   uint16_t* frag = nullptr;    // k2 rounded up to 16, x hidden x 3
-  int* bad = nullptr;          // set once W1 holds a value beyond the bf16 terms' range
+  int* bad = nullptr;          // set once W1 holds a value that three bf16 terms do not carry
   int head_blocks = 0, max_splits = 0;
 };
 // Fills frag from theta.
