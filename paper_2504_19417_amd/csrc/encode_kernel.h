@@ -385,17 +385,16 @@ __device__ inline void kstep_compute(int ks, int nsteps, const uint4* sb, const 
   constexpr int NTW = S::NTW;
   const int g = lane >> 4;
   if constexpr (MTV > 0) {
-    if constexpr (!G) cw.fetch(runs_l, vol2, rb, ks, g);
+    if constexpr (!G) {
+      cw.fetch(runs_l, vol2, rb, ks, g);
+    } else {  // (from bits requested a step ago)
+      cw.gather(ks * 4 + g, reinterpret_cast<const int2*>(runs_l), rr);
+      if (ks + 1 < nsteps) cw.bits_ahead((ks + 1) * 4 + g, rr);
+    }
     // pair sums and differences of counts at +o / -o: the -o run comes out
     // of the pair layout descending and half-swapped
     half8 cS[MTV], cD[MTV];
     pair_sums<MTV>(cw, cS, cD);
-    if constexpr (G)
-      if (ks + 1 < nsteps)
-      {
-        cw.bits_ahead((ks + 1) * 4 + g, rr);
-        cw.gather((ks + 1) * 4 + g, reinterpret_cast<const int2*>(runs_l), rr);
-      }
     const half8 bw = *reinterpret_cast<const half8*>(wts_l + ks * 32 + 8 * g);
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) {
@@ -451,7 +450,6 @@ __device__ inline void chunk_ksteps(int nsteps, const uint4* frag, uint4* slab,
   CountWords<MTV> cw;
   if constexpr (G && MTV > 0) {
     cw.bits_ahead(lane >> 4, rr);
-    cw.gather(lane >> 4, reinterpret_cast<const int2*>(runs_l), rr);
   }
   if constexpr (kEncPairSteps && NBUF == 4) {
     // two k-steps per barrier: the slabs of the next pair go into the two
