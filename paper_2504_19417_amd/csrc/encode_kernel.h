@@ -78,6 +78,8 @@ struct EncArgs {
   float2* rowflow;      // one flow per row
 };
 
+// Marks the rows of a work item after which its block has no other to take.
+constexpr int kLastItem = 1 << 30;
 // Dwords of a single row's bits: 16 per run, padded to an odd multiple of 4
 // dwords so that the 16 rows of a tile read from different banks.
 constexpr int kLutDwords = 512;
@@ -917,8 +919,11 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
   int32_t* runs_l = reinterpret_cast<int32_t*>(slab + NBUF * SLAB_U4);
   int32_t* runs1_l = runs_l + a.nsteps * 8;
   uint16_t* wts_l = reinterpret_cast<uint16_t*>(runs1_l + a.nsteps * 8);
-  int32_t* rowbase = reinterpret_cast<int32_t*>(wts_l + a.nsteps * 32);
-  int32_t* item = rowbase + CH;
+  // (a box voxel index has 16 bits: the other half of the rows' space keeps the plan)
+  uint16_t* rowbase = wts_l + a.nsteps * 32;
+  int4* plan_l = reinterpret_cast<int4*>(rowbase + CH);
+  static_assert(CH * 2 >= 2 * sizeof(int4) && CH % 8 == 0, "the plan fits behind the rows");
+  int32_t* item = reinterpret_cast<int32_t*>(rowbase + 2 * CH);
   // Count box as overlapping fp16 pairs: dword i holds the counts of box
   // voxels i and i + 1 of the same x row, so any run of 4 consecutive voxels
   // is two aligned dword reads.  Box rows are kRunPad voxels wider than the
@@ -939,6 +944,37 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
   const int KP = a.nsteps * 32;
   const int BV = a.b.bx * a.b.by * a.b.bt;
   const int D = a.D;
+  // Work items are numbered: bricks in longest-first order, one at a time
+  // (taking the next brick ahead of time upsets the balance of long jobs and
+  // measured slower on sparse batches too); between those of several chunks and
+  // the rest, the items of up to plan[5] single rows.  A block starts with the
+  // item of its own number and takes the others from a shared counter, which no
+  // block asks when there is none left for it: with the counter asked for every
+  // item, the blocks of a call met at it and a small call waited 4 to 10 us for
+  // its first item (a sliding window of 10k-event bins at D = 32: encoder 41.8
+  // us, with numbered first items 22.7 us).  A brick's record holds all it needs; the slice
+  // descriptors are in LDS.
+  int4* item4 = reinterpret_cast<int4*>(item);
+  // (one thread, the one that wrote plan_l)
+  auto put_item = [&](int it) __attribute__((always_inline)) {
+    const int4 p = plan_l[0], r = plan_l[1];
+    const int rows = p.x, items = p.z, first = p.w, whole = r.x, per = r.y, nlong = r.z;
+    const int ns = items - whole;
+    int4 e = make_int4(-1, 0, 0, 0);
+    if (it >= nlong && it < nlong + ns) {
+      const int f = (it - nlong) * per;
+      const int left = rows - first - f;
+      e = make_int4(kSparseTag, left < per ? left : per, first + f, f);
+    } else if (it < items) {
+      e = a.order[it < nlong ? it : it - ns];
+    }
+    if (items <= (int)gridDim.x) e.y |= kLastItem;
+    item4[0] = e;
+  };
+  // (the plan waits in LDS: held in registers across items, it costs the k-steps
+  // some; read from memory for every item it is another latency before its record)
+  const int4* plan4 = reinterpret_cast<const int4*>(a.plan);
+  const int4 plan_p = plan4[0], plan_r = plan4[1];  // (on their way while LDS is filled)
   for (int k = tid; k < KP / 4; k += NW * 64) {
     runs_l[k] = a.runs[k];
     runs1_l[k] = a.runs1 ? a.runs1[k] : 0;  // (no single rows without it)
@@ -954,12 +990,6 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
     }
   }
 
-  // Work items come from a shared counter: bricks in longest-first order, one
-  // at a time (taking the next brick ahead of time upsets the balance of long
-  // jobs and measured slower on sparse batches too); between those of several
-  // chunks and the rest, the items of up to plan[5] single rows.  A brick's record holds all it needs;
-  // the slice descriptors are in LDS.
-  int4* item4 = reinterpret_cast<int4*>(item);
   UnitRing ring;
   if constexpr (enc_pipelined(L)) {
     ring.src = reinterpret_cast<const unsigned char*>(a.frag) + wid * 1024;
@@ -969,27 +999,18 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
 #pragma unroll
     for (int v = 0; v < 3; ++v) issue_unit<NA, NT, L>(ring, wid, lane);
   }
+  if (tid == 0) {
+    plan_l[0] = plan_p;
+    plan_l[1] = plan_r;
+    put_item((int)blockIdx.x);
+  }
   for (;;) {
-    if (tid == 0) {
-      // (the plan is read again for every item: held across items, it costs the
-      // k-steps registers)
-      const int it = atomicAdd(&a.plan[1], 1);
-      const int ns = a.plan[2] - a.plan[4], nlong = a.plan[6];
-      int4 e = make_int4(-1, 0, 0, 0);
-      if (it >= nlong && it < nlong + ns) {
-        const int per = a.plan[5], f = (it - nlong) * per;
-        const int left = a.plan[0] - a.plan[3] - f;
-        e = make_int4(kSparseTag, left < per ? left : per, a.plan[3] + f, f);
-      } else if (it < a.plan[2]) {
-        e = a.order[it < nlong ? it : it - ns];
-      }
-      item4[0] = e;
-    }
     lds_barrier();
     const int4 cur = item4[0];
     const int bid = __builtin_amdgcn_readfirstlane(cur.x);
     if (bid < 0) break;
-    const int nq = __builtin_amdgcn_readfirstlane(cur.y);
+    const int nq = __builtin_amdgcn_readfirstlane(cur.y) & ~kLastItem;
+    const bool last = (__builtin_amdgcn_readfirstlane(cur.y) & kLastItem) != 0;  // (uniform)
     const int row0 = __builtin_amdgcn_readfirstlane(cur.z);
     const int si = __builtin_amdgcn_readfirstlane(cur.w);
     const bool single = (bid & kSparseTag) != 0;  // (uniform)
@@ -1206,7 +1227,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         const int li = a.ulist[(int64_t)bid * BV + rr];
         const int sx = __builtin_ctz(a.b.bx), sy = __builtin_ctz(a.b.by);  // (powers of two)
         const int lx = li & (a.b.bx - 1), ly = (li >> sx) & (a.b.by - 1), lt = li >> (sx + sy);
-        rowbase[r] = ((lt + a.rt) * a.SY + (ly + a.ry)) * a.SX + (lx + a.rx + kRunPad);
+        rowbase[r] = (uint16_t)(((lt + a.rt) * a.SY + (ly + a.ry)) * a.SX + (lx + a.rx + kRunPad));
       }
       // first slabs of the table (the pipelined layouts' are on their way)
       if constexpr (enc_pipelined(L)) {
@@ -1362,7 +1383,9 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         }
       }
     }
-    lds_barrier();
+    if (last) break;
+    lds_barrier();  // (the next item's rows, box and record take this one's place)
+    if (tid == 0) put_item((int)gridDim.x + atomicAdd(&a.plan[1], 1));
   }
   // (no copy into LDS outlives the block)
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -1392,10 +1415,23 @@ static int launch_rows(const EncArgs& a, const EncodeTables& et, int num_cus, hi
   const void* fn = reinterpret_cast<const void*>(&k_encode<NA, NT, L, NBUF, ROWS>);
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return VECKM_E_HIP;
-  const int per_cu = (int)((160 * 1024) / lds);
+  // as many blocks as a CU holds at once, by LDS and by the kernel's registers
+  // (a block that has to wait for another's end would hold back the item of its
+  // number: 16 waves of more than 64 registers fit once)
+  static const int by_regs = [] {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_encode<NA, NT, L, NBUF, ROWS>,
+                                                        EncShape<NA, NT, L>::NW * 64, 0) == hipSuccess)
+      return n;
+    (void)hipGetLastError();
+    return 1;
+  }();
+  const int per_cu = std::min((int)((160 * 1024) / lds), by_regs);
   int grid = num_cus * (per_cu < 1 ? 1 : (per_cu > 2 ? 2 : per_cu));
-  // no more blocks than items: whole bricks, or 16 single rows or more
-  const int items = std::max(b.bt.nbricks, (b.bt.m + 15) / 16);
+  // no more blocks than items: bricks of sp rows or more and items of 16 single
+  // rows or more (the last one aside), or every brick with a row
+  const int sp = single_rows_below(b.bt, et, num_cus, b.bt.s0.tshift != 0);
+  const int items = sp > 0 ? b.bt.m / std::min(sp, 16) + 1 : std::min(b.bt.nbricks, b.bt.m);
   if (grid > items) grid = items;
   constexpr int threads = EncShape<NA, NT, L>::NW * 64;
   hipLaunchKernelGGL((k_encode<NA, NT, L, NBUF, ROWS>), dim3(grid), dim3(threads), lds, s, b);

@@ -901,11 +901,10 @@ static void launch_brick_scan(const Batch& bt, const Workspace& w, const Brick& 
 
 // The scan and the list of single rows.
 static void launch_work_list(const Batch& bt, const Workspace& w, const EncodeTables& et,
-                             int num_cus, bool single, hipStream_t s) {
+                             int num_cus, int sp, hipStream_t s) {
   SparseRows sr;
-  if (single && et.sp > 0) {
-    // (calls of at most a full item per CU: every brick of less than one chunk)
-    sr.sp = (int64_t)bt.m <= (int64_t)et.rs * num_cus ? std::max(et.sp, et.rs + 1) : et.sp;
+  if (sp > 0) {
+    sr.sp = sp;
     sr.rs = et.rs;
     sr.cus = num_cus;
     sr.ulist = ulist_of(w);
@@ -1164,7 +1163,7 @@ int launch_prepare(const Batch& bt, const Workspace& w, const veckm_event* ev,
     launch_rank_lines(bt, w, et.brick, queries == nullptr, s);
   else
     launch_rank(bt, w, et.brick, queries == nullptr, s);
-  launch_work_list(bt, w, et, num_cus, pairs, s);
+  launch_work_list(bt, w, et, num_cus, pairs ? single_rows_below(bt, et, num_cus, false) : 0, s);
   // the paper form needs each row's voxel (and its expansion reads the query
   // -> row map); the other forms find rows as they expand
   if (!pairs && bt.m > 0)
@@ -1211,8 +1210,7 @@ int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event
                        et.brick, (uint8_t*)nullptr);
   }
   launch_rank(bt, w, et.brick, false, s);
-  // (a plane number has 15 bits in a single row's record)
-  launch_work_list(bt, w, et, num_cus, bt.s0.T < 1 << 15, s);
+  launch_work_list(bt, w, et, num_cus, single_rows_below(bt, et, num_cus, true), s);
   return hipGetLastError() == hipSuccess ? VECKM_OK : VECKM_E_HIP;
 }
 

@@ -1,6 +1,7 @@
 // Internal declarations of the veckm library (not part of the C-ABI).
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -227,6 +228,15 @@ struct EncodeTables {
   Brick bits{32, 16, 8};
   int d = 0;
 };
+
+// The rows from which on the encoder takes a brick of this call whole (0: every
+// brick).  Calls of at most a full item of single rows per CU: a chunk's, so that
+// their rows spread over the CUs.  A plane number has 15 bits in a single row's
+// record, so windows of more planes take every brick whole.
+inline int single_rows_below(const Batch& bt, const EncodeTables& et, int num_cus, bool window) {
+  if (et.sp <= 0 || (window && bt.s0.T >= 1 << 15)) return 0;
+  return (int64_t)bt.m <= (int64_t)et.rs * num_cus ? std::max(et.sp, et.rs + 1) : et.sp;
+}
 
 // Row formats the encoder writes (one row of 2D values per query voxel) and
 // the perceptron forms that read them.
