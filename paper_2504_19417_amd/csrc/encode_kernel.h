@@ -906,8 +906,21 @@ __device__ inline SliceDesc uniform(SliceDesc s) {
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 half4v __attribute__((ext_vector_type(4)));
 
+// The kernel's arguments, read again from where it is called (scalar loads from
+// the argument segment): used straight from the parameter they are all loaded
+// at the kernel's start and held, or spilled, across the k-steps.  Scalar spills
+// at D = 32, 256 and 128 (FP16 form) 136, 137 and 158, so 26, 38 and 60; 5M-event
+// slice 2.50 to 2.44 ms, 900k events at D = 256 2.22 to 2.14 ms (FP32 form).
+__device__ inline __attribute__((always_inline)) const EncArgs& encode_args() {
+  typedef __attribute__((address_space(4))) const EncArgs* args_ptr;
+  args_ptr p = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const EncArgs*)p;
+}
+
 template <int NA, int NT, int L, int NBUF, int ROWS>
-__global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
+__global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs) {
+  const EncArgs& a = encode_args();
   using S = EncShape<NA, NT, L>;
   constexpr int NW = S::NW, NTW = S::NTW, WN = S::WN, WM = S::WM, MT = S::MT, CH = S::CH,
                 SLAB_U4 = S::SLAB_U4, PFW = S::PFW;
@@ -957,6 +970,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
   int4* item4 = reinterpret_cast<int4*>(item);
   // (one thread, the one that wrote plan_l)
   auto put_item = [&](int it) __attribute__((always_inline)) {
+    const EncArgs& a = encode_args();
     const int4 p = plan_l[0], r = plan_l[1];
     const int rows = p.x, items = p.z, first = p.w, whole = r.x, per = r.y, nlong = r.z;
     const int ns = items - whole;
@@ -1005,6 +1019,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
     put_item((int)blockIdx.x);
   }
   for (;;) {
+    const EncArgs& a = encode_args();
     lds_barrier();
     const int4 cur = item4[0];
     const int bid = __builtin_amdgcn_readfirstlane(cur.x);
@@ -1019,6 +1034,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
     // single rows use the box's space: the bit table, the rows' heads, their bits
     uint4* heads = reinterpret_cast<uint4*>(vol2 + kLutDwords);
     if (single) {
+      const EncArgs& a = encode_args();
       // ---- single rows (from bricks with few rows): no count box; each row's
       //      window is collected as bits, so a chunk is full whatever bricks
       //      its rows are from, and sparse windows cost little memory traffic
@@ -1154,6 +1170,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         }
       }
     } else {
+      const EncArgs& a = encode_args();
       // ---- the brick's count box, as overlapping fp16 pairs, from the counts
       const SliceDesc sl =
           uniform(a.bt.nslices == 1 ? a.bt.s0 : a.lds_slices ? stab[si] : a.bt.table[si]);
@@ -1219,6 +1236,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
     }
 
     for (int c0 = 0; c0 < nq; c0 += CH) {
+      const EncArgs& a = encode_args();
       const int nr = nq - c0 < CH ? nq - c0 : CH;  // rows in this chunk
       const int ntiles = (nr + 15) / 16;          // 16-row tiles holding rows
       // ---- voxel of each row (row q*16 + l of the chunk; padding reuses row 0)
@@ -1313,6 +1331,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
                                                    rb, rr, accR, accI, cnt, wn, wid, lane);
       }
 
+      const EncArgs& out_args = encode_args();
       // ---- normalise by the neighbour count and write the rows: the lane
       //      holds frequencies 16 nt + 4 (lane >> 4) + (0..3) of row lane & 15
 #pragma unroll
@@ -1324,7 +1343,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
         n += __shfl_xor(n, 16);
         n += __shfl_xor(n, 32);
         if (r >= nr) continue;
-        if (a.rowcnt && wn == 0 && lane < 16) a.rowcnt[row0 + c0 + r] = (int)n;
+        if (out_args.rowcnt && wn == 0 && lane < 16) out_args.rowcnt[row0 + c0 + r] = (int)n;
         const float rc = __builtin_amdgcn_rcpf(n);
         // x / n: reciprocal estimate plus one residual correction (exact for
         // x = n, so an all-ones feature still gives exactly 1).  A query of a
@@ -1349,7 +1368,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
           // before they reach HBM (streaming stores measured 1.4-2x the
           // row bytes in HBM writes)
           if constexpr (ROWS == kRowsBF16) {
-            uint16_t* out = static_cast<uint16_t*>(a.rows);
+            uint16_t* out = static_cast<uint16_t*>(out_args.rows);
             u32x2 pr, pi;
             pr.x = pack_bf16x2(re[0], re[1]);
             pr.y = pack_bf16x2(re[2], re[3]);
@@ -1363,7 +1382,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
             // of 4 consecutive row elements becomes one 16-byte unit [hi x 4,
             // lo x 4], so a row keeps the fp32 row's size and a lane writes
             // one unit for its 4 real and one for its 4 imaginary parts.
-            _Float16* out = static_cast<_Float16*>(a.rows);
+            _Float16* out = static_cast<_Float16*>(out_args.rows);
             const int64_t u2 = u * 2;
             half8 ur, ui;
 #pragma unroll
@@ -1376,7 +1395,7 @@ __global__ __launch_bounds__(enc_waves(L) * 64) void k_encode(EncArgs a) {
             *reinterpret_cast<half8*>(out + u2 + 2 * j) = ur;
             *reinterpret_cast<half8*>(out + u2 + 2 * (D + j)) = ui;
           } else {
-            float* out = static_cast<float*>(a.rows);
+            float* out = static_cast<float*>(out_args.rows);
             *reinterpret_cast<floatx4*>(out + u + j) = re;
             *reinterpret_cast<floatx4*>(out + u + D + j) = im;
           }
