@@ -676,7 +676,7 @@ int veckm_create(const veckm_params* params, veckm_ctx** out) {
     t.runs1 = druns1;
     t.rs = encode_single_rows(t);
     t.sp = druns1 && t.rs >= 16 && single_rows_fit(params->width, params->height, t.bits)
-               ? kSparseBelow
+               ? std::min(kSparseBelow, t.rs * 3 / 4)
                : 0;
     c->tilings.push_back(t);
   }

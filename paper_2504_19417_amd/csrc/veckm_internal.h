@@ -74,11 +74,15 @@ constexpr int kMaxBrickVoxels = 8192;  // largest brick (the ranking kernel's li
 // Work items of the encoder that hold single rows carry this bit in their
 // brick field (brick numbers stay below it).
 constexpr int kSparseTag = 1 << 30;
-// Bricks with fewer rows than this go to the encoder row by row.  A full chunk
-// of single rows costs about 1.2 of a brick's, a brick's chunk costs its box
-// and the better part of a full chunk's time however few rows it holds.  Whole
-// call with 80 / 128 / 176: 64 lognormal slices 4.59 / 4.41 / 4.44 ms, 5M-event
-// slice 2.54 / 2.54 / 2.61 ms, 1M-event slice (FP16 form) 0.359 / 0.358 / 0.365 ms.
+// Bricks with fewer rows than this, and than three quarters of the single rows an
+// item holds, go to the encoder row by row.  A full item of single rows costs
+// about 1.2 of a brick's chunk, a brick's chunk costs its box and the better part
+// of a full chunk's time however few rows it holds.  Whole call with 96 / 128 /
+// 160 at 256 rows per item and more: 64 lognormal slices 4.31 / 4.29 / 4.32 ms,
+// 5M-event slice 2.44 / 2.46 / 2.50 ms, 1M-event slice (FP16 form) 344 / 345 /
+// 347 us, 200k events at D = 128 171 / 166 / 167 us.  With 32 / 48 / 64 / 128 at
+// 80 (r = 5/3) and 64 (r = 6/3) rows per item (900k events, D = 256, FP32 form):
+// 2029 / 2018 / 2027 / 2182 and 2326 / 2319 / 2333 / 2582 us.
 constexpr int kSparseBelow = 128;
 std::vector<Tiling> tiling_candidates(int rx, int ry, int rt, int d, int precision, int kp);
 size_t encode_lds_need(int d, int precision, int nbuf, int kp, int vol, int layout = 0);
