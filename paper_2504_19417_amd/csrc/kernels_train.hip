@@ -614,18 +614,17 @@ int launch_train_step(const TrainState& s, const float* x, const float* y, int64
 #undef VECKM_FWD
   }
   if (rc) return rc;
-  // dW1 = dZ^T X, split over rows: about one block per CU, at least 64 rows each
-  const int hq = hid / 64, ny = hq > 4 ? 2 : 1, ta = (hq + ny - 1) / ny;
-  const int tb = k2 > 128 ? 2 : 1, nx = (int)nblocks(k2, 128 * tb);
+  // dW1 = dZ^T X, split over rows
+  const TrainTiles tt = train_tiles(hid, k2, m);
   const int64_t tiles = nblocks(m, 32);
-  const int per = (int)std::max<int64_t>(2, nblocks(tiles, std::max(1, s.max_splits / (nx * ny))));
-  const int nsplit = (int)nblocks(tiles, per);
-  const dim3 grid(nx, ny, nsplit);
-  switch (ta) {
-    case 1: launch_dw1<1>(s, tb, grid, m, per, x, st); break;
-    case 2: launch_dw1<2>(s, tb, grid, m, per, x, st); break;
-    case 3: launch_dw1<3>(s, tb, grid, m, per, x, st); break;
-    default: launch_dw1<4>(s, tb, grid, m, per, x, st); break;
+  const int per = (int)std::max<int64_t>(2, nblocks(tiles, tt.max_splits));
+  const int nsplit = (int)nblocks(tiles, per);  // (at most max_splits, the size of w1_part)
+  const dim3 grid(tt.nx, tt.ny, nsplit);
+  switch (tt.ta) {
+    case 1: launch_dw1<1>(s, tt.tb, grid, m, per, x, st); break;
+    case 2: launch_dw1<2>(s, tt.tb, grid, m, per, x, st); break;
+    case 3: launch_dw1<3>(s, tt.tb, grid, m, per, x, st); break;
+    default: launch_dw1<4>(s, tt.tb, grid, m, per, x, st); break;
   }
   EndArgs e;
   e.nw1 = (int64_t)hid * k2;

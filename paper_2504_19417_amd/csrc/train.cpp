@@ -19,7 +19,6 @@ struct veckm_trainer {
 namespace {
 
 constexpr int kHeadBlocks = 512;
-constexpr int kMaxSplits = 256;  // row splits of dW1, times its tiles per split
 
 void free_state(TrainState& s) {
   void* bufs[] = {s.theta, s.m1, s.m2, s.dZ, s.head_part, s.w1_part, s.frag, s.bad};
@@ -50,11 +49,8 @@ int veckm_trainer_create(int32_t d, int32_t hidden, int64_t max_rows, const floa
   s.hidden = hidden;
   s.max_rows = max_rows;
   s.head_blocks = kHeadBlocks;
-  s.max_splits = kMaxSplits;
   const int64_t np = (int64_t)hidden * s.k2 + 3 * (int64_t)hidden + 2;
-  const int64_t row_tiles = (max_rows + 31) / 32;
-  // (a step splits the rows over at most kMaxSplits blocks in all, at least two row tiles each)
-  const int64_t splits = std::min<int64_t>(kMaxSplits, (row_tiles + 1) / 2);
+  const int64_t splits = train_tiles(hidden, s.k2, max_rows).max_splits;
   auto alloc = [](auto** p, int64_t count) {
     return dev_malloc(reinterpret_cast<void**>(p), (size_t)count * sizeof(**p));
   };

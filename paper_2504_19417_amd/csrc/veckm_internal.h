@@ -348,6 +348,24 @@ int launch_window_prepare(const Batch& bt, const Workspace& w, const veckm_event
 
 // ------------------------------------------------------------ perceptron training
 constexpr int kTrainBlockRows = 256;  // most rows a block of the forward kernel takes
+// The tiles of dW1 (64 ta units x 128 tb features each, nx x ny of them) and the
+// most row splits a step takes of them: about one block per CU in all, at least
+// two row tiles of 32 per split.
+struct TrainTiles {
+  int ta, tb, nx, ny;
+  int64_t max_splits;
+};
+inline TrainTiles train_tiles(int hidden, int k2, int64_t max_rows) {
+  TrainTiles t;
+  const int hq = hidden / 64;
+  t.ny = hq > 4 ? 2 : 1;
+  t.ta = (hq + t.ny - 1) / t.ny;
+  t.tb = k2 > 128 ? 2 : 1;
+  t.nx = (k2 + 128 * t.tb - 1) / (128 * t.tb);
+  const int64_t row_tiles = (max_rows + 31) / 32;
+  t.max_splits = std::min<int64_t>(std::max(1, 256 / (t.nx * t.ny)), (row_tiles + 1) / 2);
+  return t;
+}
 // Device state of a trainer: parameters in the order W1 [hidden][k2], b1, W2
 // [2][hidden], b2, Adam moments, the gradients of the layer-1 pre-activations
 // for max_rows rows (in the order of the matrix-core accumulators), W1 as
@@ -363,7 +381,7 @@ struct TrainState {
   float* w1_part = nullptr;    // row splits x hidden x k2
   uint16_t* frag = nullptr;    // k2 rounded up to 16, x hidden x 3
   int* bad = nullptr;          // set once W1 holds a value that three bf16 terms do not carry
-  int head_blocks = 0, max_splits = 0;
+  int head_blocks = 0;
 };
 // Fills frag from theta.
 int launch_train_init(const TrainState& s, void* stream);

@@ -98,3 +98,17 @@ def test_tiny_weights(vk, m, d, hidden):
     p["b1"] = _fixed_masks(x, p["W1"])
     _, got, _, new = _step(vk, x, y, p, 2.0 ** 122)
     _check(got, new, p, ("W2",))
+
+
+def test_device_memory_of_a_small_batch_trainer(vk):
+    """The partial sums of W1 are sized for the row splits a step takes: 64 of 1 MB
+    at D = 256 and 512 units (4 tiles of 256 x 256), beside 42 MB for the rows."""
+    d, hidden, rows = 256, 512, 20_000
+    torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    tr = vk.Trainer(d, hidden, rows, *synth.init_mlp(d, hidden))
+    used = before - torch.cuda.mem_get_info()[0]
+    tr.close()
+    need = 64 * hidden * 2 * d * 4 + 79 * 256 * hidden * 4
+    assert used <= need + (32 << 20), (used, need)
