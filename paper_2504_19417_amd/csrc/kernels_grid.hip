@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void k_rank_lines(Batch bt, Brick b,
   if (lane == 0) brick_nq[gb] = base;
 }
 
-// k_rank_lines for dense calls (most bricks hold many rows): the same work
+// k_rank_lines for bricks that hold many rows (rank_by_blocks): the same work
 // with one block per brick, each of its NW waves taking an equal run of the
 // brick's voxel steps, in order; the ballots of the query voxels go to LDS,
 // one barrier gives every wave its offset, and a second pass writes the
@@ -510,8 +510,7 @@ __global__ __launch_bounds__(NW * 64) void k_rank_lines4(Batch bt, Brick b,
   }
 }
 
-// The count grid of a dense call back to zero in one pass (cheaper than the
-// per-event stores when the grid is small beside the events; see dense_batch).
+// The count grid back to zero in one pass (see dense_batch).
 __device__ inline void fill_zero(int blk, int nblk, int32_t* __restrict__ a, int64_t n) {
   const int64_t stride = (int64_t)nblk * blockDim.x;
   for (int64_t i = (int64_t)blk * blockDim.x + threadIdx.x; i < n; i += stride) a[i] = 0;
@@ -1014,8 +1013,8 @@ __global__ void k_expand_flow_q(const int32_t* __restrict__ queries, Batch bt, B
   expand_flow_q<SUB>(blockIdx.x, queries, bt, b, vox, rank, brick_off, rowflow, out);
 }
 
-// The flows of a dense call and the clear of its count grid in one
-// launch: blocks [0, eb) expand, the others zero the grid.  The
+// The flows of a call and the clear of its count grid in one
+// launch (dense_batch): blocks [0, eb) expand, the others zero the grid.  The
 // expansion does not read it, so the two parts need no order,
 // and the call saves a launch.
 template <bool SUB>
@@ -1083,40 +1082,45 @@ static void launch_rank(const Batch& bt, const Workspace& w, const Brick& b, boo
     big ? go(k_rank<false, 32>) : go(k_rank<false, 16>);
 }
 
-// Small calls whose bricks hold some rows also rank a brick per block, of 8
-// waves: all blocks run at once, and a wave visits one group of voxel steps
-// instead of up to eight in turn.  20k events in 748 bricks: the whole call
-// 71.7 to 59.9 us; 500 events in 187 bricks (one group per brick at most) are
-// better off with a wave each, 46.6 against 48.8 us.
-constexpr int kBlockBricks = 2048, kBlockEvents = 8;
+// Whether the bricks are ranked by a block each, which walks all voxel steps of a
+// brick at once, or by a wave each, which walks its rows that hold events 16 at a
+// time: blocks where bricks are large (inside the slice) and hold many events, and
+// the more events the more blocks have to take turns.  Whole call, block against
+// wave, with bricks of 32 x 16 x 8 (events per brick):
+//   187 bricks of 2.4k voxels: 35.9 / 37.5 us (11), 37.2 / 41.8 (27), 54.8 / 68.7 (214)
+//   187 bricks of 1 bin: 34.6 / 33.4 (3), 35.7 / 35.2 (16); of 2: 34.5 / 34.1 (5),
+//     37.1 / 38.7 (27), 41.5 / 45.1 (107), 56.0 / 60.3 (321)
+//   374 bricks: 35.6 / 36.0 (4), 36.1 / 38.2 (8); 600: 38.8 / 37.5 (7), 40.3 / 43.0 (17)
+//   748 bricks: 38.5 / 36.2 (4), 39.1 / 39.2 (8), 40.6 / 43.0 (16)
+//   1309 bricks: 48.5 / 46.7 (15), 60.0 / 62.2 (38), 83.0 / 89.4 (76)
+//   1800 bricks: 50.3 / 46.9 (11), 62.6 / 63.0 (28), 83.5 / 87.5 (56); of 2 bins:
+//     50.4 / 44.9 (11), 63.1 / 57.5 (33), 115.8 / 110.3 (222)
+//   3600 bricks: 97.8 / 97.0 (28), 202 / 212 (194); 4200: 161.7 / 157.5 (71), 295 / 301 (238)
+//   12600 bricks: 293 / 255 (40), 426 / 394 (79), 879 / 863 (317)
+static bool rank_by_blocks(const Batch& bt) {
+  const int64_t nb = bt.nbricks, n = bt.n;
+  return nb <= 8192 && n >= 6 * nb && 48 * n >= nb * nb && bt.nvox >= nb * (nb <= 1024 ? 768 : 1536);
+}
 
 static void launch_rank_lines(const Batch& bt, const Workspace& w, const Brick& b, bool all,
                               hipStream_t s) {
-  // dense calls: a block per brick; else a wave per brick (latency-bound
-  // sparse bricks)
-  auto go = [&](auto fn, unsigned blocks, size_t lds) {
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(256), lds, s, bt, b, w.count, w.lines, w.qmark,
-                       w.rank, ulist_of(w), w.brick_nq, w.pairs,
-                       reinterpret_cast<uint2*>(brick_bits(w)), w.err);
-  };
-  auto go8 = [&](auto fn, unsigned blocks) {
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(512), 0, s, bt, b, w.count, w.lines, w.qmark,
+  auto go = [&](auto fn, unsigned blocks, unsigned threads, size_t lds) {
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(threads), lds, s, bt, b, w.count, w.lines, w.qmark,
                        w.rank, ulist_of(w), w.brick_nq, w.pairs,
                        reinterpret_cast<uint2*>(brick_bits(w)), w.err);
   };
   const unsigned nb = (unsigned)bt.nbricks, nb4 = (unsigned)((bt.nbricks + 3) / 4);
   const size_t rows_lds = 4 * (size_t)b.by * b.bt * sizeof(uint16_t);  // (at most 16 KiB)
-  const bool spread = !dense_batch(bt) && bt.nbricks <= kBlockBricks &&
-                      (int64_t)bt.n >= kBlockEvents * (int64_t)bt.nbricks;
-  if (dense_batch(bt) || spread) {
-    // (8 waves for the largest bricks: with a quarter of the blocks, 4 waves
-    // each left the kernel latency-bound)
-    if (b.volume() > 4096 || spread)
-      all ? go8(k_rank_lines4<true, 8>, nb) : go8(k_rank_lines4<false, 8>, nb);
+  if (rank_by_blocks(bt)) {
+    // blocks of 8 waves where all run at once (1309 bricks: 83.2 against 83.0 us with
+    // 4 waves, 1800: 111.4 against 110.3; 187: 54.8 against 58.1), and for the largest
+    // bricks (with a quarter of the blocks, 4 waves each left the kernel latency-bound)
+    if (b.volume() > 4096 || bt.nbricks <= 1024)
+      all ? go(k_rank_lines4<true, 8>, nb, 512, 0) : go(k_rank_lines4<false, 8>, nb, 512, 0);
     else
-      all ? go(k_rank_lines4<true, 4>, nb, 0) : go(k_rank_lines4<false, 4>, nb, 0);
+      all ? go(k_rank_lines4<true, 4>, nb, 256, 0) : go(k_rank_lines4<false, 4>, nb, 256, 0);
   } else {
-    all ? go(k_rank_lines<true>, nb4, rows_lds) : go(k_rank_lines<false>, nb4, rows_lds);
+    all ? go(k_rank_lines<true>, nb4, 256, rows_lds) : go(k_rank_lines<false>, nb4, 256, rows_lds);
   }
 }
 

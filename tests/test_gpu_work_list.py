@@ -92,3 +92,45 @@ def test_slices_that_share_tiles(vk, count, n):
         off += len(e)
     assert c.status() == vk.VECKM_OK
     c.close()
+
+
+@pytest.mark.parametrize("W,H,T,n", [
+    (346, 260, 1, 3000), (346, 260, 2, 900), (346, 260, 2, 2500), (346, 260, 10, 2000),
+    (346, 260, 10, 3000), (346, 260, 50, 33_000), (346, 260, 50, 38_000), (640, 480, 50, 360_000),
+    (640, 480, 50, 380_000), (1280, 720, 60, 30_000), (100, 60, 300, 20_000), (640, 480, 6, 8000),
+])
+def test_ranking_and_clearing_routes(vk, W, H, T, n):
+    """Both sides of the rules that choose how bricks are ranked (a wave or a block
+    each, of 4 or 8 waves) and how the count grid is cleared (with the flows, in one
+    pass, by events): a call after another on the same context gives what a fresh
+    context gives, and sampled encodings match the oracle."""
+    print("case: routes %dx%dx%d n=%d" % (W, H, T, n), file=sys.stderr, flush=True)
+    rx, ry, rt, d, t0 = 3, 3, 1, 64, 5
+    A = synth.draw_frequencies(d, rx, ry, rt, nbins=T)
+    mlp = synth.init_mlp(d, 128)
+    evs = [_events(9100 + n + k, W, H, T, n, t0) for k in range(2)]
+    q = np.random.Generator(np.random.PCG64(n)).integers(0, n, 500).astype(np.int32)
+
+    def calls(c, e):
+        out = [c.flow(e, t0, T), c.encode(e, t0, T), c.flow(e, t0, T, queries=torch.from_numpy(q).cuda())]
+        assert c.status() == vk.VECKM_OK
+        return out
+
+    def context():
+        c = vk.Context(W, H, rx, ry, rt, A, T, n, "fp32")
+        c.set_mlp(*mlp)
+        return c
+
+    dev = [torch.from_numpy(e).cuda() for e in evs]
+    used, fresh = context(), context()
+    first = calls(used, dev[0])
+    second = calls(used, dev[1])
+    for a, b in zip(second, calls(fresh, dev[1])):
+        assert torch.equal(a, b)
+    for a, b in zip(first, calls(used, dev[0])):
+        assert torch.equal(a, b)
+    assert torch.equal(first[2], first[0][torch.from_numpy(q).cuda().long()])
+    ref, _ = oracle.encode(evs[0], A, rx, ry, rt, queries=q)
+    assert _rel(first[1].cpu().numpy()[q], ref) <= 1e-6
+    used.close()
+    fresh.close()
