@@ -1014,7 +1014,7 @@ __global__ void k_expand_flow_q(const int32_t* __restrict__ queries, Batch bt, B
 }
 
 // The flows of a call and the clear of its count grid in one
-// launch (dense_batch): blocks [0, eb) expand, the others zero the grid.  The
+// launch (fill_with_flows): blocks [0, eb) expand, the others zero the grid.  The
 // expansion does not read it, so the two parts need no order,
 // and the call saves a launch.
 template <bool SUB>
@@ -1263,7 +1263,7 @@ int launch_expand_flow(const Batch& bt, const Workspace& w, const int32_t* queri
 
 int launch_expand_flow_clear(const Batch& bt, const Workspace& w, const int32_t* queries,
                              const Brick& b, float* flow, void* stream) {
-  if (!dense_batch(bt)) return VECKM_E_INVAL;
+  if (!fill_with_flows(bt)) return VECKM_E_INVAL;
   const int eb = bt.m > 0 ? blocks_for(bt.m, 256) : 0;
   const dim3 grid(eb + fill_grid(bt.nvox));
   const float2* rf = reinterpret_cast<const float2*>(w.rowflow);

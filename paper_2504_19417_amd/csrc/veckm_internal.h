@@ -313,19 +313,26 @@ int launch_mlp(const Workspace& w, const MlpWeights& mw, int d, int rows, int nu
 bool mlp_rows_split(int d, int hidden);
 int launch_expand_flow(const Batch& bt, const Workspace& w, const int32_t* queries,
                        const Brick& b, bool use_qmap, float* flow, void* stream);
-// The flows of a dense bounded-window slice call (dense_batch) and the clear
-// of its count grid, in one launch (launch_expand_flow followed by
-// launch_clear_events); VECKM_E_INVAL for a call that is not dense.
+// The flows of a bounded-window slice call and the clear of its count grid, in one
+// launch (launch_expand_flow followed by launch_clear_events), where
+// fill_with_flows; VECKM_E_INVAL elsewhere.
 int launch_expand_flow_clear(const Batch& bt, const Workspace& w, const int32_t* queries,
                              const Brick& b, float* flow, void* stream);
 // Per-query neighbour counts from the rows' counts (int32 [U], held in
 // w.rowflow); -1 for an invalid query.
 int launch_expand_count(const Batch& bt, const Workspace& w, const int32_t* queries,
                         const Brick& b, int32_t* counts, void* stream);
-// Whether a bounded-window slice call is dense: its grids hold fewer than 30
-// entries per event.  Dense calls clear the count grid with one pass over it
-// (per-event stores take longer) and rank a brick per block.
-inline bool dense_batch(const Batch& bt) { return bt.nvox + bt.npairs < 30 * (int64_t)bt.n; }
+// Whether a bounded-window slice call clears its count grid with one pass over it
+// (else its events' voxels one by one).  Whole call, one pass against events: 4.5M
+// voxels with 100k / 200k / 300k events 83.7 / 103.3 / 119.0 against 83.2 / 104.3 /
+// 120.8 us, 46M voxels with 1M / 2M 406 / 588 against 394 / 593 us.
+inline bool dense_batch(const Batch& bt) { return bt.nvox < 30 * (int64_t)bt.n; }
+// Whether the flows of such a call and the clear share a launch
+// (launch_expand_flow_clear): also on small grids, whose pass takes less than a
+// launch (1.8M voxels, 2k / 20k events 35.3 / 50.3 against 36.2 / 51.6 us, 2.5M
+// voxels 20k events 43.5 against 44.4; 6.1M voxels, 20k events 53.1 against 51.7).
+constexpr int64_t kFillVoxels = 5 << 19;
+inline bool fill_with_flows(const Batch& bt) { return dense_batch(bt) || bt.nvox <= kFillVoxels; }
 // After a bounded-window slice call whose launches all went through: the
 // counts of its events' voxels back to zero (the ranking kernel has cleared
 // the row flags).
