@@ -332,8 +332,8 @@ def serving_sweep(vk, seconds, scales=(0.5, 1.0, 2.0)):
 
 
 KERNEL_SOURCES = {  # kernel name prefix (template form) -> source file it is built from
-    "k_encode<4": "paper_2504_19417_amd/csrc/kernels_encode.hip",   # FP32 form encoder
-    "k_encode<2": "paper_2504_19417_amd/csrc/kernels_encode.hip",   # FP16 form encoder
+    "k_encode<4": "paper_2504_19417_amd/csrc/encode_kernel.h",   # FP32 form encoder
+    "k_encode<2": "paper_2504_19417_amd/csrc/encode_kernel.h",   # FP16 form encoder
     "k_mlp_res<2": "paper_2504_19417_amd/csrc/kernels_mlp.hip",     # FP32 form perceptron
     "k_mlp_split<": "paper_2504_19417_amd/csrc/kernels_mlp.hip",    # FP32 form, paper form
     "k_mlp_res<0": "paper_2504_19417_amd/csrc/kernels_mlp.hip",     # FP16 form perceptron

@@ -281,7 +281,7 @@ void veckm_graph_destroy(veckm_graph* graph);
                             3: 8 waves of 2 row tiles and 4: 16 waves of
                             one row tile (D <= 128), each wave over every
                             frequency of its rows, loads pipelined within
-                            the wave, one slab in flight, the perceptron
+                            the wave over a ring of half slabs, the perceptron
                             inside the encoder at D = 64 and 128)
                             of tiling `index` (host int32[5])
      veckm_tiling_select    use tiling `index` from the next call on

@@ -364,7 +364,7 @@ int run(veckm_ctx* c, const Workspace& w, const Batch& bt, const veckm_event* ev
   // a window's encode: ev holds the query events, the counts are resident
   if (bt.m == 0) return VECKM_OK;
   // rows the encoder hands to the perceptron (encodings handed out are fp32)
-  // (the one-wave-per-SIMD tiling runs the perceptron itself: no rows at all)
+  // (the pipelined tilings run the perceptron themselves: no rows at all)
   const bool fused = flow && !c->paper && c->mw.W1frag && encode_fusable(c->et, c->mw.hidden);
   const int rows = !flow                             ? kRowsF32
                    : fused                            ? (c->p.precision == VECKM_FP16 ? kFlowBF16
@@ -1205,7 +1205,7 @@ int veckm_flow_noalloc(veckm_ctx* ctx, const veckm_event* events, int64_t n, int
   if (rc) return rc;
   if (ctx->mw.hidden == 0) return VECKM_E_STATE;
   if (n == 0) return VECKM_OK;
-  Workspace w = ctx->w;  // tables, zero page and error flag stay the context's
+  Workspace w = ctx->w;  // tables and error flag stay the context's
   if (carve_noalloc(ctx, bt, nullptr, &w) > (int64_t)VECKM_NOALLOC_SCRATCH_BYTES)
     return VECKM_E_BUDGET;
   unsigned char* base = nullptr;

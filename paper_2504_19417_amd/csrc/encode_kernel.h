@@ -19,17 +19,17 @@
 //
 // Work decomposition: the (x, y, t) grid of every slice is cut into bricks,
 // and the bricks of all slices of a call form one work list.  A persistent
-// block takes items from a device counter: a brick that holds many query
-// voxels is taken whole (its counts plus the window halo copied from the pair
-// grid into LDS, its query voxels in chunks of up to 512 rows, 256 at D = 128),
-// the rows of all other bricks in full chunks of single rows, each with its own
+// block takes the item of its number, then items from a device counter: a brick
+// that holds many query voxels is taken whole (its counts plus the window halo
+// read from the count grid into LDS as fp16 pairs, its query voxels in chunks of up
+// to 512 rows, 256 at D = 128), the rows of all other bricks in full chunks of single rows, each with its own
 // window.  The table streams through LDS, shared by the block's waves.
 //
 // Why single rows: a chunk costs its pass over the table whatever it holds, and
 // a brick its box (70 KB at r = 5/3).  64 slices of 10k events have 5 rows per
 // brick, 64 lognormal slices 33: with every brick (or items of 13 single rows
 // with a count box each) the encoder took 4.96 ms (FP32 form) and 10.8 ms (FP16
-// form) there, with full chunks 0.69 and 3.2 ms.
+// form) there, with full chunks 0.67 and 3.2 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -58,7 +58,7 @@ struct EncArgs {
   const uint2* bits;  // per brick x row: low and high bits of its voxels' counts (brick_bits)
   const int4* order;  // work list of whole bricks: {brick, rows, first row, slice}
   const int2* srow;   // {slice, slice-local voxel} of each single row
-  const int32_t* runs1;  // the runs' offsets, packed (pack_run)
+  const int32_t* runs1;  // the runs' offsets, packed (make_run_triples)
   int lds_slices;     // slices whose descriptors are copied to LDS (0: read them from global)
   const uint4* frag;     // the phase table's slabs, then W1's (hidden / 32, make_w1_fragments)
   const int32_t* runs;
@@ -360,20 +360,11 @@ __device__ inline void pair_sums(const CountWords<MTV>& cw, half8 (&cS)[MTV > 0 
   }
 }
 
-// The k-steps of one chunk for a wave that holds MTV valid 16-row tiles
-// (0 <= MTV <= MT; no per-tile branches inside).  Every wave runs it: a wave
-// without rows still moves its share of each slab and meets every barrier.
-// On entry the first slab is in LDS and the next NBUF - 2 are in flight.
-//
-// The table is the MFMA A operand and the counts the B operand, so that the
-// accumulator of a lane holds 4 consecutive frequencies of one row (the
-// lane's row is lane & 15): the count of that row arrives in the same lane
-// and the row is written with 16-byte stores.
 // One k-step of the contraction for a wave with MTV valid row tiles: the
 // count pair sums of its rows (gathered from the box), the table slab `sb`
 // as A operand, and the exact neighbour count on the vector ALU.
-// (G: of single rows, whose count words `cw` were gathered a step ahead; the
-// next step's are requested here).
+// (G: of single rows, whose count words are looked up from bits requested in the
+// step before; the next step's are requested here).
 template <int NA, int NT, int L, int MTV, bool G>
 __device__ inline void kstep_compute(int ks, int nsteps, const uint4* sb, const int32_t* runs_l,
                                      const uint16_t* wts_l, const uint32_t* vol2,
@@ -535,9 +526,9 @@ __device__ inline void chunk_ksteps_n(int mtv, int nsteps, const uint4* frag, ui
 // 2048 against 2048.  What then remains beside the products is vector work that
 // both waves of a SIMD do at the same time (pair sums, the division by the
 // count), so that is spread between products where it can be (layer 2 runs
-// behind the next tile's products).  1M-event slice, encoder and perceptron:
-// FP32 form 0.56 to 0.52 ms, FP16 form 0.37 to 0.29 ms against one slab ahead
-// in the 16-wave layout.  Each accumulator receives exactly the products of
+// behind the next tile's products).  1M-event slice, encoder and perceptron, when
+// it replaced one slab ahead in the 16-wave layout: FP32 form 0.56 to 0.52 ms,
+// FP16 form 0.37 to 0.29 ms (0.48 and 0.28 ms in passes of one case now).  Each accumulator receives exactly the products of
 // layouts 0 and 1 in the same order: results are bit-identical.
 
 // The unit stream of a block's wave (all wave-uniform): units lie back to back
@@ -909,7 +900,7 @@ typedef _Float16 half4v __attribute__((ext_vector_type(4)));
 // The kernel's arguments, read again from where it is called (scalar loads from
 // the argument segment): used straight from the parameter they are all loaded
 // at the kernel's start and held, or spilled, across the k-steps.  Scalar spills
-// at D = 32, 256 and 128 (FP16 form) 136, 137 and 158, so 26, 38 and 60; 5M-event
+// at D = 32, 256 and 128 (FP16 form) 114, 133 and 151, so 26, 37 and 60; 5M-event
 // slice 2.50 to 2.44 ms, 900k events at D = 256 2.22 to 2.14 ms (FP32 form).
 __device__ inline __attribute__((always_inline)) const EncArgs& encode_args() {
   typedef __attribute__((address_space(4))) const EncArgs* args_ptr;
@@ -1479,7 +1470,7 @@ static int launch_t(const EncArgs& a, const EncodeTables& et, int rows, int num_
 template <int NA, int NT, int L>
 static int launch_nb(const EncArgs& a, const EncodeTables& et, int rows, int num_cus,
                      hipStream_t s) {
-  if constexpr (enc_pipelined(L)) {  // the pipelined layouts keep one slab in flight
+  if constexpr (enc_pipelined(L)) {  // a ring of four half slabs: the space of two
     if (et.nbuf != 2) return VECKM_E_INVAL;
     return launch_t<NA, NT, L, 2>(a, et, rows, num_cus, s);
   } else {

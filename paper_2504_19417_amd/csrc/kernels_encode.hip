@@ -117,7 +117,7 @@ int launch_encode(const Batch& bt, const Workspace& w, const EncodeTables& et, i
   a.pairs = w.pairs;
   a.rows = w.rows;
   a.plan = w.plan;
-  if (a.SX > 64) return VECKM_E_INVAL;  // one wavefront copies one box row
+  if (a.SX > 64) return VECKM_E_INVAL;  // 16 lanes of 4 voxels read a box row, within kGridPad
   if (et.sp > 0 && (!et.runs1 || !w.srow || et.rs > encode_single_rows(et))) return VECKM_E_INVAL;
   hipStream_t s = (hipStream_t)stream;
   return et.na == 4 ? dispatch_nt<4>(a, et, rows, num_cus, s)

@@ -535,8 +535,9 @@ __global__ void k_clear_events(Batch bt, const int32_t* __restrict__ vox,
 // first: 64 or more, 32-63, 16-31, 12-15, 8-11, then 7, 6, ..., 1 exactly;
 // longest job first keeps the persistent encoder's tail short) and by brick
 // number within a class.  plan[0] = U, plan[1] = 0 (the encoder's work counter),
-// plan[2] = number of non-empty bricks.  Three launches: per-tile totals,
-// a scan of the tile totals, then each tile places its bricks.  Within a
+// plan[2] = number of work items.  Three launches (one up to kScanTile bricks):
+// per-tile totals, a scan of the tile totals, then each tile places its bricks
+// and lists its single rows.  Within a
 // tile thread t owns bricks [t kScanPer, (t + 1) kScanPer); nothing is
 // counted with atomics, so order[] is the same on every call.
 constexpr int kScanClasses = 12;  // kScanNV = class counts, then rows of the

@@ -303,7 +303,7 @@ std::vector<Tiling> tiling_candidates(int rx, int ry, int rt, int d, int precisi
   // more per wave: D >= 64), where they fit: 8 waves of 4 row tiles over half
   // the frequencies (1); 4 (2), 8 (3) or, at D <= 128, 16 (4) waves over
   // every frequency of their rows, whose loads are pipelined within each
-  // wave with one slab in flight (and whose encoder can run the perceptron
+  // wave over a ring of half slabs (and whose encoder can run the perceptron
   // itself)
   const size_t n = out.size();
   for (int layout = 1; layout <= 4; ++layout)

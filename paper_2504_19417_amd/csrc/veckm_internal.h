@@ -253,7 +253,7 @@ constexpr int kRowsHiLo16 = 3;   // rows written as fp16 hi/lo pairs by the enco
                                  // (FP32 form)
 // The encoder runs the perceptron itself and writes one flow per row (no
 // rows leave the chip): bf16 operands (FP16 form) or fp16 hi/lo operands
-// (FP32 form).  Only with the one-wave-per-SIMD layout at D = 64 or 128.
+// (FP32 form).  Only with the pipelined layouts at D = 64 or 128.
 constexpr int kFlowBF16 = 4;
 constexpr int kFlowHiLo16 = 5;
 
