@@ -418,15 +418,15 @@ PROFILE_NOTES = {
                "kernel's last 60 dispatches (those three passes; the first few tens of calls "
                "after start run up to 12 % slower).  The encoders run the "
                "perceptron themselves (template arguments: operand terms, slab tiles, wave "
-               "layout, ring depth, row format): `k_encode<4, 8, 4, 2, 5>` is the FP32 form "
-               "(16 waves, fp16 hi/lo operands, 32x16x8 brick), `k_encode<2, 8, 4, 2, 4>` the "
-               "FP16/BF16 form (16 waves, bf16 perceptron, 32x16x16 brick); the other encoder "
+               "layout, ring depth, row format): `k_encode<4, 8, 3, 2, 5>` is the FP32 form "
+               "(8 waves, fp16 hi/lo operands, 32x16x8 brick), `k_encode<2, 8, 3, 2, 4>` the "
+               "FP16/BF16 form (8 waves, bf16 perceptron, 32x16x16 brick); the other encoder "
                "instances are tuner trials; the front-end and expansion kernels serve both.  "
                "`__amd_rocclr_*` are runtime copies and fills outside the steps.",
     "paper_k8": "Three runs of 2 warm-up + 5 timed steps: FP32 form over all events, FP16/BF16 "
                 "form over all events, FP32 form over the 10k-query subset (7 calls each).  "
-                "`k_paper_rows<false>` and `k_mlp_split` serve the FP32 runs (all events and 10k "
-                "queries: hence the min/max spread), `k_paper_rows<true>` and `k_mlp_res` the "
+                "`k_mlp_split` (which forms the rows itself) serves the FP32 runs (all events and "
+                "10k queries: hence the min/max spread), `k_paper_rows<true>` and `k_mlp_res` the "
                 "FP16/BF16 run; `k_tphase`, `k_pool2d`, the box sums and the prepare kernels "
                 "serve all three.",
 }
@@ -436,7 +436,7 @@ PROFILE_NOTES["precision5m"] = (
     "and perceptron), 2 warm-up and 5 timed steps.  Template arguments of `k_encode`: operand "
     "terms (2: FP16/BF16 form, 4: FP32 form's hi/lo), slab tiles, wave layout, ring depth, row "
     "format (1: bf16 rows, 3: hi/lo rows, both for `k_mlp_res`; 4 and 5: perceptron inside the "
-    "encoder, bf16 and hi/lo operands).  The fused `<2, 8, 4, 2, 4>` (16 waves, 32x32x8 brick "
+    "encoder, bf16 and hi/lo operands).  The fused `<2, 8, 3, 2, 4>` (8 waves, 32x16x16 brick "
     "in this run) and `<4, 8, 3, 2, 5>` (8 waves, 32x16x8 brick) are the tuner's picks and run "
     "the timed "
     "steps (the same template names also cover tuner trials on other bricks); the rest are "
@@ -447,11 +447,11 @@ PROFILE_NOTES["batch64"] = (
     "encoder and perceptron), 1 warm-up and 3 timed steps.  Template arguments of "
     "`k_encode`: operand terms (2: FP16/BF16 form, 4: FP32 form's hi/lo), slab tiles, wave "
     "layout, ring depth, row format (0-3: rows written for `k_mlp_res`; 4, 5: perceptron "
-    "inside the encoder).  The tuner's picks on this batch write rows in wave layout 0: "
-    "`k_encode<2, 8, 0, 2, 1>` (FP16 form, 32x32x8 brick) and `k_encode<4, 8, 0, 2, 3>` "
-    "(FP32 form, 32x16x8), with `k_mlp_res` after them; the other encoder instances are "
+    "inside the encoder).  The tuner's picks on this batch run the perceptron in the encoder: "
+    "`k_encode<2, 8, 3, 2, 4>` (FP16 form, 8 waves, 32x32x8 brick) and `k_encode<4, 8, 4, 2, 5>` "
+    "(FP32 form, 16 waves, 32x16x8); the other encoder instances and `k_mlp_res` are "
     "tuner trials.  `k_rank_lines` ranks the flagged rows of the batch's bricks (a wave per "
-    "brick: the batch is sparse), `k_clear_events` returns the grids to zero after each "
+    "brick: the batch is sparse), `k_clear_events` returns the count grid to zero after each "
     "call, and the brick scan runs as three launches (`k_scan_totals`, `k_scan_tiles`, "
     "`k_scan_place`).  The front-end kernels serve both forms and the tuner runs.")
 
