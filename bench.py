@@ -55,15 +55,15 @@ def encode_stage_flops_per_row(K, d, hidden, stages):
     return encoder_flops_per_row(K, d) + (mlp_flops_per_row(d, hidden) if fused else 0), fused
 
 
-def paper_encode_bytes(W, H, T, d, rows, row_bytes):
+def paper_encode_bytes(W, H, T, d):
     """Algorithmic HBM bytes of the paper form's encode stage (no temporal
     bound): the temporal phase pass reads the T x H x W count grid and writes
     the complex D-wide fp32 pixel grid G; the fused window pass reads G and
-    writes S; the box sums read and write four int32 pixel grids; the row
-    pass reads S (8D bytes) and writes one row per query voxel."""
+    writes S; the box sums read and write four int32 pixel grids.  (The rows
+    are formed inside the perceptron in the FP32 form.)"""
     V2 = W * H
     grid = 2 * d * 4 * V2
-    return 4 * T * V2 + grid + 2 * grid + 4 * 4 * V2 + rows * (2 * d * 4 + row_bytes)
+    return 4 * T * V2 + grid + 2 * grid + 4 * 4 * V2
 
 
 def eqn18_split(n, m_small, ms_small, ms_all):
@@ -655,12 +655,11 @@ def paper_main(args, name):
 
     st32, st16 = stages(res["fp32"]), stages(res["fp16"])
     rows = res["fp32"]["rows"]
-    enc_bytes = paper_encode_bytes(W, H, T, w.d, rows, 2 * w.d * 4)
+    enc_bytes = paper_encode_bytes(W, H, T, w.d)
     cand = {
         "encode": dict(ms=st32["encode"], bound="hbm", amount=enc_bytes / 1e9,
                        peak=PEAK["hbm_GBps"], unit="GB/s",
-                       kernel="paper encode stage (k_tphase, k_pool2d, k_boxx, k_boxy, "
-                              "k_paper_rows)"),
+                       kernel="paper encode stage (k_tphase, k_pool2d, k_boxx, k_boxy)"),
         "mlp": dict(ms=st32["mlp"], bound="mfma", amount=mlp_flops_per_row(w.d, w.hidden) * rows / 1e12,
                     peak=PEAK["fp16_TFLOPs"], unit="TFLOP/s", kernel="k_mlp_split<"),
     }
@@ -1015,12 +1014,11 @@ def train_main(args):
         "config": {"workload": "train", "rows": m, "d": w.d, "hidden": hid,
                    "optimizer": "adam", "lr": 1e-3},
         "loss": {"after_warmup": l0, "after_steps": l1},
-        "roofline": {"bound": "alu", "achieved": round(flops / dt / 1e12, 2),
-                     "peak": 78.6, "unit": "TFLOP/s",
-                     "frac": round(flops / dt / 1e12 / 78.6, 4), "traffic": None,
-                     "kernel": "training step (fp32 FMA GEMMs on the vector ALU, without "
-                               "packed-fp32 instructions: 256 CUs x 4 SIMDs x 16 lanes x 2 flops "
-                               "x 2.4 GHz = 78.6 TFLOP/s)"},
+        "roofline": {"bound": "mfma", "achieved": round(6 * flops / dt / 1e12, 2),
+                     "peak": PEAK["fp16_TFLOPs"], "unit": "TFLOP/s",
+                     "frac": round(6 * flops / dt / 1e12 / PEAK["fp16_TFLOPs"], 4), "traffic": None,
+                     "kernel": "training step (each fp32 product as six bf16 products on the "
+                               "matrix cores)"},
         "cpu_baseline": None,
     }
     print(json.dumps(line), flush=True)
