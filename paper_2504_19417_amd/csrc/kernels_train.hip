@@ -28,9 +28,10 @@
 // stored; the error against 64 bits is the same.
 // A tile whose operands hold a value that three bf16 terms do not carry is
 // computed again on the fp32 matrix cores, which treat it as fp32 arithmetic
-// does: an infinity, a NaN, |v| >= 2^127 (h may round to infinity), or 0 < |v|
-// < 2^-110 (its last bit lies under bf16's smallest number, 2^-133, so l would
-// lose bits; both matrix cores keep subnormal operands, products and sums).
+// does: an infinity, a NaN, |v| >= 2^127 (h may round to infinity), or a value
+// under 2^-110 whose last bits lie under bf16's smallest number, 2^-133, so that
+// l would lose them (both matrix cores keep subnormal operands, products and
+// sums).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,32 +45,33 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr uint32_t kHuge = 0x7f000000u;  // 2^127
-constexpr uint32_t kTiny = 0x08800000u;  // 2^-110
-
-// The extent of the magnitudes seen (as bits; a zero counts as neither end).
+// What was seen of the values split so far: the largest magnitude (as bits), and
+// the bits of the last remainders, whose lower half is zero where they are bf16
+// numbers (the third term carries them whole).
 struct Extent {
-  uint32_t big = 0, low = ~0u;
-  __device__ inline void take(float v) {
+  uint32_t big = 0, rest = 0;
+  __device__ inline void take(float v, float r2) {
     const uint32_t mag = __float_as_uint(v) & 0x7fffffffu;
     big = mag > big ? mag : big;
-    low = mag - 1 < low ? mag - 1 : low;
+    rest |= __float_as_uint(r2);
   }
-  __device__ inline bool beyond_terms() const { return big >= kHuge || low < kTiny - 1; }
+  __device__ inline bool beyond_terms() const { return big >= kHuge || (rest & 0xffffu) != 0; }
 };
 
-// The three bf16 terms of 8 fp32 values, and what those values extend over.
+// The three bf16 terms of 8 fp32 values, and what was seen of those.
 struct Split8 {
   bf16x8 t[3];
   __device__ inline void make(const float (&v)[8], Extent& ext) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      ext.take(v[e]);
       const __bf16 h = (__bf16)v[e];
       const float r1 = v[e] - (float)h;
       const __bf16 m = (__bf16)r1;
+      const float r2 = r1 - (float)m;
       t[0][e] = h;
       t[1][e] = m;
-      t[2][e] = (__bf16)(r1 - (float)m);
+      t[2][e] = (__bf16)r2;
+      ext.take(v[e], r2);
     }
   }
 };
@@ -87,13 +89,14 @@ __device__ inline floatx16 mfma_split(const bf16x8 (&a)[3], const bf16x8 (&b)[3]
 // W1's fragments (the B operand of layer 1): per 16-feature k-step, 32-unit
 // tile and bf16 term, lane l holds features 8 (l >> 5) + (0..7) of unit l & 31.
 __device__ inline void put_w1_frag(uint16_t* frag, int nt, int hid, int k, float w, int* bad) {
-  Extent ext;
-  ext.take(w);
-  if (ext.beyond_terms()) *bad = 1;  // (stays set: layer 1 runs in fp32)
   const __bf16 h = (__bf16)w;
   const float r1 = w - (float)h;
   const __bf16 m = (__bf16)r1;
-  const __bf16 t[3] = {h, m, (__bf16)(r1 - (float)m)};
+  const float r2 = r1 - (float)m;
+  const __bf16 t[3] = {h, m, (__bf16)r2};
+  Extent ext;
+  ext.take(w, r2);
+  if (ext.beyond_terms()) *bad = 1;  // (stays set: layer 1 runs in fp32)
   const int lane = ((k >> 3) & 1) * 32 + (hid & 31);
   uint16_t* p = frag + (((int64_t)(k >> 4) * nt + (hid >> 5)) * 3 * 64 + lane) * 8 + (k & 7);
 #pragma unroll
